@@ -16,9 +16,9 @@
 //     q_e = rho w~_e / (RMS(w~_e) + eps) with rho = 1 (Eq. rcr_direction_prototype),
 //     a~ = ||f_e(q_e)|| / (||q_e|| + eps) with f_e the SwiGLU expert applied to
 //     q_e as its input (Eq. rcr_raw_amplification), A = a~ / (mean a~ + eps)
-//     (Eq. rcr_layer_normalization).  One workgroup per expert, fp64 VALU
-//     (about 3 m d multiply-adds per expert).  The same pass accumulates
-//     ||G||_F^2 and ||U||_F^2 for GSP.
+//     (Eq. rcr_layer_normalization).  fp64 VALU (about 3 m d multiply-adds per
+//     expert), rows spread over the chip: h, then W_down h.  The pass over W_gate
+//     and W_up also gives each row's share of ||G||_F^2 and ||U||_F^2 for GSP.
 // Every reduction has a fixed order, so the tables are deterministic; fp64
 // throughout, they agree with an fp64 evaluation to ~1e-15 relative.
 #include "ace_internal.h"
@@ -29,9 +29,10 @@ namespace {
 
 typedef double f64x4_t __attribute__((ext_vector_type(4)));
 
-// 8 consecutive elements as raw storage; element i as a double
-template <typename T> struct Raw8;
-template <> struct Raw8<bf16_t> {
+// 16 bytes of consecutive elements as raw storage; element i as a double
+template <typename T> struct Vec;
+template <> struct Vec<bf16_t> {
+  static constexpr int n = 8;
   uint4 v;
   __device__ __forceinline__ void load(const bf16_t *p) { v = *reinterpret_cast<const uint4 *>(p); }
   __device__ __forceinline__ double at(int i) const {
@@ -39,17 +40,28 @@ template <> struct Raw8<bf16_t> {
     return static_cast<double>(__uint_as_float((i & 1) ? (w & 0xFFFF0000u) : (w << 16)));
   }
 };
-template <> struct Raw8<float> {
-  float4 lo, hi;
-  __device__ __forceinline__ void load(const float *p) {
-    lo = *reinterpret_cast<const float4 *>(p);
-    hi = *reinterpret_cast<const float4 *>(p + 4);
-  }
+template <> struct Vec<float> {
+  static constexpr int n = 4;
+  float4 v;
+  __device__ __forceinline__ void load(const float *p) { v = *reinterpret_cast<const float4 *>(p); }
   __device__ __forceinline__ double at(int i) const {
-    const float4 &h = i < 4 ? lo : hi;
-    const int j = i & 3;
-    return static_cast<double>(j == 0 ? h.x : j == 1 ? h.y : j == 2 ? h.z : h.w);
+    return static_cast<double>(i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w);
   }
+};
+
+// two consecutive elements
+template <typename T> struct Pair;
+template <> struct Pair<bf16_t> {
+  uint32_t v;
+  __device__ __forceinline__ void load(const bf16_t *p) { v = *reinterpret_cast<const uint32_t *>(p); }
+  __device__ __forceinline__ double at(int i) const {
+    return static_cast<double>(__uint_as_float(i ? (v & 0xFFFF0000u) : (v << 16)));
+  }
+};
+template <> struct Pair<float> {
+  float2 v;
+  __device__ __forceinline__ void load(const float *p) { v = *reinterpret_cast<const float2 *>(p); }
+  __device__ __forceinline__ double at(int i) const { return static_cast<double>(i ? v.y : v.x); }
 };
 
 __device__ __forceinline__ double to_f64(bf16_t v) { return static_cast<double>(bf16_to_f32(v)); }
@@ -61,9 +73,11 @@ struct TabArgs {
   double eps, rho;
   double *pair_part;  // [N][n_pairs][2]: sum(D o G), sum(D o U) of each tile pair
   double *wbar;       // [d] mean router row
-  double *rcr_raw;    // [N]
-  double *norm2;      // [N][2]: ||G||_F^2, ||U||_F^2
-  double *gsp_raw;    // [N]
+  double *h;          // [N][m] SwiGLU activation of the prototype
+  double *row_norm2;  // [N][m][2]: squared norms of row i of G and of U
+  double *f_part;     // [N][d / 32]: sums of f_e(q_e)^2 over 32 outputs
+  double *q_norm;     // [N] ||q_e||
+  double *gsp_raw, *rcr_raw;  // [N]
   float *a_gsp, *a_rcr;
   double *a_gsp64, *a_rcr64;
 };
@@ -74,11 +88,27 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-// grid (tile pairs, experts), 4 waves; wave (wr, wc) owns a 32 x 32 sub-tile
+// Sums of D o G and D o U over one 64 x 64 tile pair of one expert, 4 waves;
+// wave (wr, wc) owns a 32 x 32 sub-tile.  Bound by the fp64 matrix cores: a wave
+// issues 12 MFMAs of 64 cycles per 4 k, so its operand loads (straight from L2,
+// no LDS) only have to be covered by the other wave of its SIMD; the launch bound
+// keeps two waves per SIMD resident (one wave alone stalled at every K block:
+// 12.25 ms for 128 experts of 768 x 2048, now 9.18 ms, 51 TFLOP/s in fp64 where a
+// 4096^3 library product reaches 62).
+// gamma enters one operand of each product as gamma^2 (exact in fp64: 8 or 24 + 16
+// or 48 bits against one weight), which halves the fp64 multiplies.  Row r of a
+// sub-tile's 16-row block u is row 2 r + u, so W_down is read in adjacent column
+// pairs.  In a diagonal tile the sub-tile below the diagonal mirrors the one above
+// it: its wave does nothing and the other counts twice.
 template <typename T>
-__global__ __launch_bounds__(256) void gsp_tile_kernel(TabArgs a) {
-  const int e = blockIdx.y;
-  int p = blockIdx.x, bi = 0;
+__global__ __launch_bounds__(256, 2) void gsp_tile_kernel(TabArgs a) {
+  constexpr int KL = Vec<T>::n;  // consecutive k of a lane
+  // experts dealt to the 8 XCDs, so the tile pairs of one expert share its weights in one L2
+  const int b = blockIdx.x >> 3;
+  const int e = (blockIdx.x & 7) + 8 * (b / a.n_pairs);
+  if (e >= a.N) return;
+  int p = b % a.n_pairs, bi = 0;
+  const int pair = p;
   while (p >= a.mt - bi) {
     p -= a.mt - bi;
     ++bi;
@@ -89,78 +119,90 @@ __global__ __launch_bounds__(256) void gsp_tile_kernel(TabArgs a) {
   const int wr = wave >> 1, wc = wave & 1;
   const int d = a.d, m = a.m;
   const size_t eo = static_cast<size_t>(e) * m * d;
-  const T *Wg = static_cast<const T *>(a.w_gate) + eo;
-  const T *Wu = static_cast<const T *>(a.w_up) + eo;
-  const T *Wd = static_cast<const T *>(a.w_down) + eo;  // [d, m]
-  const T *gam = static_cast<const T *>(a.gamma);
-  int ri[2], cj[2];
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    ri[u] = bi * 64 + wr * 32 + 16 * u + r16;
-    cj[u] = bj * 64 + wc * 32 + 16 * u + r16;
-  }
-  f64x4_t accD[2][2], accG[2][2], accU[2][2];
-#pragma unroll
-  for (int u = 0; u < 2; ++u)
-#pragma unroll
-    for (int v = 0; v < 2; ++v) accD[u][v] = accG[u][v] = accU[u][v] = f64x4_t{0.0, 0.0, 0.0, 0.0};
-
-  // 32-wide K blocks; lane group g holds k = k0 + 8 g + j and MFMA j takes element j
-  for (int k0 = 0; k0 < d; k0 += 32) {
-    const int kb = k0 + 8 * g;
-    Raw8<T> gm, ga[2], gb[2], ua[2], ub[2];
-    gm.load(gam + kb);
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      ga[u].load(Wg + static_cast<size_t>(ri[u]) * d + kb);
-      gb[u].load(Wg + static_cast<size_t>(cj[u]) * d + kb);
-      ua[u].load(Wu + static_cast<size_t>(ri[u]) * d + kb);
-      ub[u].load(Wu + static_cast<size_t>(cj[u]) * d + kb);
-    }
-    T da[2][8], db[2][8];  // W_down[k][col] for the 8 k of this lane group
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        da[u][j] = Wd[static_cast<size_t>(kb + j) * m + ri[u]];
-        db[u][j] = Wd[static_cast<size_t>(kb + j) * m + cj[u]];
-      }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const double gj = gm.at(j);
-      double xa[2], xb[2], ya[2], yb[2], za[2], zb[2];
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        xa[u] = ga[u].at(j) * gj;
-        xb[u] = gb[u].at(j) * gj;
-        ya[u] = ua[u].at(j) * gj;
-        yb[u] = ub[u].at(j) * gj;
-        za[u] = to_f64(da[u][j]);
-        zb[u] = to_f64(db[u][j]);
-      }
-#pragma unroll
-      for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int v = 0; v < 2; ++v) {
-          accG[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[u], xb[v], accG[u][v], 0, 0, 0);
-          accU[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(ya[u], yb[v], accU[u][v], 0, 0, 0);
-          accD[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(za[u], zb[v], accD[u][v], 0, 0, 0);
-        }
-    }
-  }
-  // sum(D o G), sum(D o U) over this wave's sub-tile (the three tiles share one layout)
+  const double mult = bi != bj || wr < wc ? 2.0 : wr == wc ? 1.0 : 0.0;
   double sg = 0.0, su = 0.0;
+  if (mult != 0.0) {
+    const int ia = bi * 64 + wr * 32 + 2 * r16, jb = bj * 64 + wc * 32 + 2 * r16;
+    const T *ga_p = static_cast<const T *>(a.w_gate) + eo + static_cast<size_t>(ia) * d + KL * g;
+    const T *gb_p = static_cast<const T *>(a.w_gate) + eo + static_cast<size_t>(jb) * d + KL * g;
+    const T *ua_p = static_cast<const T *>(a.w_up) + eo + static_cast<size_t>(ia) * d + KL * g;
+    const T *ub_p = static_cast<const T *>(a.w_up) + eo + static_cast<size_t>(jb) * d + KL * g;
+    const T *da_p = static_cast<const T *>(a.w_down) + eo + static_cast<size_t>(KL * g) * m + ia;  // [d, m]
+    const T *db_p = static_cast<const T *>(a.w_down) + eo + static_cast<size_t>(KL * g) * m + jb;
+    const T *gam = static_cast<const T *>(a.gamma) + KL * g;
+    f64x4_t accD[2][2], accG[2][2], accU[2][2];
 #pragma unroll
-  for (int u = 0; u < 2; ++u)
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
-    for (int v = 0; v < 2; ++v)
+      for (int v = 0; v < 2; ++v) accD[u][v] = accG[u][v] = accU[u][v] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+
+    // blocks of 4 KL k: lane group g holds k = k0 + KL g + j and MFMA j takes element j
+#pragma unroll 1
+    for (int k0 = 0; k0 < d; k0 += 4 * KL) {
+      Vec<T> gm, ga[2], gb[2], ua[2], ub[2];
+      Pair<T> da[KL], db[KL];  // W_down[k][col], col = the pair of columns of this lane's two blocks
+      gm.load(gam + k0);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        sg = fma(accD[u][v][i], accG[u][v][i], sg);
-        su = fma(accD[u][v][i], accU[u][v][i], su);
+      for (int u = 0; u < 2; ++u) {
+        ga[u].load(ga_p + static_cast<size_t>(u) * d + k0);
+        gb[u].load(gb_p + static_cast<size_t>(u) * d + k0);
+        ua[u].load(ua_p + static_cast<size_t>(u) * d + k0);
+        ub[u].load(ub_p + static_cast<size_t>(u) * d + k0);
       }
-  sg = wave_sum(sg);
-  su = wave_sum(su);
+#pragma unroll
+      for (int j = 0; j < KL; ++j) {
+        da[j].load(da_p + static_cast<size_t>(k0 + j) * m);
+        db[j].load(db_p + static_cast<size_t>(k0 + j) * m);
+      }
+#pragma unroll
+      for (int j = 0; j < KL; ++j) {
+        const double gj = gm.at(j), g2 = gj * gj;
+        double xa[2], xb[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          xa[u] = ga[u].at(j) * g2;
+          xb[u] = gb[u].at(j);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int v = 0; v < 2; ++v)
+            accG[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[u], xb[v], accG[u][v], 0, 0, 0);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          xa[u] = ua[u].at(j) * g2;
+          xb[u] = ub[u].at(j);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int v = 0; v < 2; ++v)
+            accU[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[u], xb[v], accU[u][v], 0, 0, 0);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          xa[u] = da[j].at(u);
+          xb[u] = db[j].at(u);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int v = 0; v < 2; ++v)
+            accD[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[u], xb[v], accD[u][v], 0, 0, 0);
+      }
+    }
+    // this wave's sub-tile (the three tiles share one layout)
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int v = 0; v < 2; ++v)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          sg = fma(accD[u][v][i], accG[u][v][i], sg);
+          su = fma(accD[u][v][i], accU[u][v][i], su);
+        }
+    sg = wave_sum(sg) * mult;
+    su = wave_sum(su) * mult;
+  }
   __shared__ double part[4][2];
   if (lane == 0) {
     part[wave][0] = sg;
@@ -168,27 +210,28 @@ __global__ __launch_bounds__(256) void gsp_tile_kernel(TabArgs a) {
   }
   __syncthreads();
   if (tid == 0) {
-    const double mult = bi == bj ? 1.0 : 2.0;
-    double tg = 0.0, tu = 0.0;
-    for (int w = 0; w < 4; ++w) {
-      tg += part[w][0];
-      tu += part[w][1];
-    }
-    double *o = a.pair_part + (static_cast<size_t>(e) * a.n_pairs + blockIdx.x) * 2;
-    o[0] = mult * tg;
-    o[1] = mult * tu;
+    double *o = a.pair_part + (static_cast<size_t>(e) * a.n_pairs + pair) * 2;
+    o[0] = ((part[0][0] + part[1][0]) + part[2][0]) + part[3][0];
+    o[1] = ((part[0][1] + part[1][1]) + part[2][1]) + part[3][1];
   }
 }
 
-// mean router row, one thread per column, experts added in order
+// mean router row: a workgroup takes 64 columns, wave w the experts w, w + 4, ...
 template <typename T>
 __global__ __launch_bounds__(256) void rcr_mean_kernel(TabArgs a) {
-  const int k = blockIdx.x * 256 + threadIdx.x;
-  if (k >= a.d) return;
+  __shared__ double part[4][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int k = blockIdx.x * 64 + lane;
   const T *W = static_cast<const T *>(a.w_router);
   double s = 0.0;
-  for (int e = 0; e < a.N; ++e) s += to_f64(W[static_cast<size_t>(e) * a.d + k]);
-  a.wbar[k] = s / a.N;
+  if (k < a.d) {
+#pragma unroll 8
+    for (int e = wave; e < a.N; e += 4) s += to_f64(W[static_cast<size_t>(e) * a.d + k]);
+  }
+  part[wave][lane] = s;
+  __syncthreads();
+  if (wave == 0 && k < a.d)
+    a.wbar[k] = (((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane]) / a.N;
 }
 
 // block-wide sum in a fixed order (wave butterflies, then waves in order)
@@ -201,96 +244,157 @@ __device__ __forceinline__ double block_sum4(double v, double *scratch) {
   return ((scratch[0] + scratch[1]) + scratch[2]) + scratch[3];
 }
 
-// one workgroup (4 waves) per expert
+// h = SiLU(W_gate q) * (W_up q) for 16 rows of one expert (wave w: rows 4 w .. 4 w + 3),
+// and the rows' shares of ||G||^2, ||U||^2.  Bound by reading the weights once, so
+// the rows are spread over N m / 16 workgroups (one workgroup per expert left half
+// the chip idle behind a serial chain of rows: 9.3 ms for 128 experts of 768 x 2048,
+// now 0.18 ms here and 0.076 ms in rcr_out_kernel).
+constexpr int kHRows = 4;  // rows of one wave
 template <typename T>
-__global__ __launch_bounds__(256) void rcr_expert_kernel(TabArgs a) {
-  extern __shared__ double h[];  // [m]
+__global__ __launch_bounds__(256) void rcr_hidden_kernel(TabArgs a) {
+  constexpr int KL = Vec<T>::n;
   __shared__ double red[4];
-  __shared__ double nrm[4][2];
-  const int e = blockIdx.x;
+  const int nb = a.m / (4 * kHRows);
+  const int e = blockIdx.x / nb, blk = blockIdx.x - e * nb;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int d = a.d, m = a.m;
   const T *wr = static_cast<const T *>(a.w_router) + static_cast<size_t>(e) * d;
   const T *gam = static_cast<const T *>(a.gamma);
-  // RMS of the centred router row and ||q||
+  // RMS of the centred router row, and ||q|| (block 0)
   double s2 = 0.0;
   for (int k = tid; k < d; k += 256) {
     const double w = to_f64(wr[k]) - a.wbar[k];
-    s2 += w * w;
+    s2 = fma(w, w, s2);
   }
   const double r = sqrt(block_sum4(s2, red) / d);
   const double inv = a.rho / (r + a.eps);
-  double q2 = 0.0;
-  for (int k = tid; k < d; k += 256) {
-    const double q = (to_f64(wr[k]) - a.wbar[k]) * inv;
-    q2 += q * q;
-  }
-  const double qn = sqrt(block_sum4(q2, red));
-  // h = SiLU(W_gate q) * (W_up q); wave w takes rows w, w + 4, ...; also ||G||^2, ||U||^2
-  const size_t eo = static_cast<size_t>(e) * m * d;
-  const T *Wg = static_cast<const T *>(a.w_gate) + eo;
-  const T *Wu = static_cast<const T *>(a.w_up) + eo;
-  double ng = 0.0, nu = 0.0;
-  for (int i = wave; i < m; i += 4) {
-    double sgi = 0.0, sui = 0.0;
-    for (int k = lane; k < d; k += 64) {
+  if (blk == 0) {  // uniform over the workgroup
+    double q2 = 0.0;
+    for (int k = tid; k < d; k += 256) {
       const double q = (to_f64(wr[k]) - a.wbar[k]) * inv;
-      const double wg = to_f64(Wg[static_cast<size_t>(i) * d + k]);
-      const double wu = to_f64(Wu[static_cast<size_t>(i) * d + k]);
-      sgi = fma(wg, q, sgi);
-      sui = fma(wu, q, sui);
-      const double gk = to_f64(gam[k]);
-      const double G = wg * gk, U = wu * gk;
-      ng = fma(G, G, ng);
-      nu = fma(U, U, nu);
+      q2 = fma(q, q, q2);
     }
-    sgi = wave_sum(sgi);
-    sui = wave_sum(sui);
-    if (lane == 0) h[i] = sgi / (1.0 + exp(-sgi)) * sui;
+    q2 = block_sum4(q2, red);
+    if (tid == 0) a.q_norm[e] = sqrt(q2);
   }
-  ng = wave_sum(ng);
-  nu = wave_sum(nu);
-  if (lane == 0) {
-    nrm[wave][0] = ng;
-    nrm[wave][1] = nu;
+  const int i0 = blk * 4 * kHRows + wave * kHRows;
+  const size_t ro = (static_cast<size_t>(e) * m + i0) * d;
+  const T *Wg = static_cast<const T *>(a.w_gate) + ro;
+  const T *Wu = static_cast<const T *>(a.w_up) + ro;
+  double sg[kHRows], su[kHRows], ng[kHRows], nu[kHRows];
+#pragma unroll
+  for (int i = 0; i < kHRows; ++i) sg[i] = su[i] = ng[i] = nu[i] = 0.0;
+  for (int k = KL * lane; k < d; k += KL * 64) {
+    Vec<T> wv, gv, g[kHRows], u[kHRows];
+    wv.load(wr + k);
+    gv.load(gam + k);
+#pragma unroll
+    for (int i = 0; i < kHRows; ++i) {
+      g[i].load(Wg + static_cast<size_t>(i) * d + k);
+      u[i].load(Wu + static_cast<size_t>(i) * d + k);
+    }
+#pragma unroll
+    for (int j = 0; j < KL; ++j) {
+      const double q = (wv.at(j) - a.wbar[k + j]) * inv, gk = gv.at(j);
+#pragma unroll
+      for (int i = 0; i < kHRows; ++i) {
+        const double wg = g[i].at(j), wu = u[i].at(j);
+        sg[i] = fma(wg, q, sg[i]);
+        su[i] = fma(wu, q, su[i]);
+        const double G = wg * gk, U = wu * gk;
+        ng[i] = fma(G, G, ng[i]);
+        nu[i] = fma(U, U, nu[i]);
+      }
+    }
   }
-  __syncthreads();
-  // f = W_down h; wave w takes rows w, w + 4, ...
-  const T *Wd = static_cast<const T *>(a.w_down) + eo;
-  double f2 = 0.0;
-  for (int rr = wave; rr < d; rr += 4) {
-    double s = 0.0;
-    for (int i = lane; i < m; i += 64) s = fma(to_f64(Wd[static_cast<size_t>(rr) * m + i]), h[i], s);
-    s = wave_sum(s);
-    f2 = fma(s, s, f2);  // identical in every lane of the wave
-  }
-  if (lane == 0) red[wave] = f2;
-  __syncthreads();
-  if (tid == 0) {
-    const double fn = sqrt(((red[0] + red[1]) + red[2]) + red[3]);
-    a.rcr_raw[e] = fn / (qn + a.eps);
-    a.norm2[2 * e] = ((nrm[0][0] + nrm[1][0]) + nrm[2][0]) + nrm[3][0];
-    a.norm2[2 * e + 1] = ((nrm[0][1] + nrm[1][1]) + nrm[2][1]) + nrm[3][1];
+#pragma unroll
+  for (int i = 0; i < kHRows; ++i) {
+    const double sgi = wave_sum(sg[i]), sui = wave_sum(su[i]);
+    const double ngi = wave_sum(ng[i]), nui = wave_sum(nu[i]);
+    if (lane == 0) {
+      const size_t o = static_cast<size_t>(e) * m + i0 + i;
+      a.h[o] = sgi / (1.0 + exp(-sgi)) * sui;
+      a.row_norm2[2 * o] = ngi;
+      a.row_norm2[2 * o + 1] = nui;
+    }
   }
 }
 
-// GSP raw values from the tile sums, then both layer normalisations
+// sum of squares of 32 outputs f = W_down h of one expert (wave w: outputs 8 w .. 8 w + 7)
+constexpr int kFRows = 8;  // outputs of one wave
+template <typename T>
+__global__ __launch_bounds__(256) void rcr_out_kernel(TabArgs a) {
+  constexpr int KL = Vec<T>::n;
+  __shared__ double red[4];
+  const int nb = a.d / (4 * kFRows);
+  const int e = blockIdx.x / nb, blk = blockIdx.x - e * nb;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int d = a.d, m = a.m;
+  const T *Wd = static_cast<const T *>(a.w_down) +
+                (static_cast<size_t>(e) * d + blk * 4 * kFRows + wave * kFRows) * static_cast<size_t>(m);
+  const double *h = a.h + static_cast<size_t>(e) * m;
+  double s[kFRows];
+#pragma unroll
+  for (int i = 0; i < kFRows; ++i) s[i] = 0.0;
+  for (int k = KL * lane; k < m; k += KL * 64) {
+    Vec<T> w[kFRows];
+#pragma unroll
+    for (int i = 0; i < kFRows; ++i) w[i].load(Wd + static_cast<size_t>(i) * m + k);
+#pragma unroll
+    for (int j = 0; j < KL; ++j) {
+      const double hj = h[k + j];
+#pragma unroll
+      for (int i = 0; i < kFRows; ++i) s[i] = fma(w[i].at(j), hj, s[i]);
+    }
+  }
+  double f2 = 0.0;  // identical in every lane of the wave
+#pragma unroll
+  for (int i = 0; i < kFRows; ++i) {
+    const double f = wave_sum(s[i]);
+    f2 = fma(f, f, f2);
+  }
+  if (lane == 0) red[wave] = f2;
+  __syncthreads();
+  if (threadIdx.x == 0) a.f_part[static_cast<size_t>(e) * nb + blk] = ((red[0] + red[1]) + red[2]) + red[3];
+}
+
+// raw GSP and RCR values of one expert: every partial sum added in a fixed order
+__global__ __launch_bounds__(256) void tables_expert_kernel(TabArgs a) {
+  __shared__ double red[4];
+  const int e = blockIdx.x, tid = threadIdx.x;
+  double dg = 0.0, du = 0.0, ng = 0.0, nu = 0.0, f2 = 0.0;
+  const double *pp = a.pair_part + static_cast<size_t>(e) * a.n_pairs * 2;
+  for (int p = tid; p < a.n_pairs; p += 256) {
+    dg += pp[2 * p];
+    du += pp[2 * p + 1];
+  }
+  const double *rn = a.row_norm2 + static_cast<size_t>(e) * a.m * 2;
+  for (int i = tid; i < a.m; i += 256) {
+    ng += rn[2 * i];
+    nu += rn[2 * i + 1];
+  }
+  const int nb = a.d / (4 * kFRows);
+  for (int i = tid; i < nb; i += 256) f2 += a.f_part[static_cast<size_t>(e) * nb + i];
+  dg = block_sum4(dg, red);
+  du = block_sum4(du, red);
+  ng = block_sum4(ng, red);
+  nu = block_sum4(nu, red);
+  f2 = block_sum4(f2, red);
+  if (tid == 0) {
+    const double a_up = sqrt(nu) * sqrt(dg);    // ||U|| ||W_d G||
+    const double a_gate = sqrt(ng) * sqrt(du);  // ||G|| ||W_d U||
+    a.gsp_raw[e] = sqrt(a_up * a_gate);
+    a.rcr_raw[e] = sqrt(f2) / (a.q_norm[e] + a.eps);
+  }
+}
+
+// both layer normalisations
 __global__ __launch_bounds__(256) void tables_finalize_kernel(TabArgs a) {
   __shared__ double red[4];
   const int tid = threadIdx.x;
   double sg_all = 0.0, sr_all = 0.0;
   for (int e = tid; e < a.N; e += 256) {
-    const double *pp = a.pair_part + static_cast<size_t>(e) * a.n_pairs * 2;
-    double dg = 0.0, du = 0.0;
-    for (int p = 0; p < a.n_pairs; ++p) {
-      dg += pp[2 * p];
-      du += pp[2 * p + 1];
-    }
-    const double a_up = sqrt(a.norm2[2 * e + 1]) * sqrt(dg);    // ||U|| ||W_d G||
-    const double a_gate = sqrt(a.norm2[2 * e]) * sqrt(du);      // ||G|| ||W_d U||
-    const double raw = sqrt(a_up * a_gate);
-    a.gsp_raw[e] = raw;
-    sg_all += raw;
+    sg_all += a.gsp_raw[e];
     sr_all += a.rcr_raw[e];
   }
   const double mg = block_sum4(sg_all, red) / a.N;
@@ -307,45 +411,63 @@ __global__ __launch_bounds__(256) void tables_finalize_kernel(TabArgs a) {
 
 template <typename T>
 void launch_tables_t(const TabArgs &a, hipStream_t stream) {
-  gsp_tile_kernel<T><<<dim3(a.n_pairs, a.N), 256, 0, stream>>>(a);
-  rcr_mean_kernel<T><<<dim3((a.d + 255) / 256), 256, 0, stream>>>(a);
-  rcr_expert_kernel<T><<<dim3(a.N), 256, static_cast<size_t>(a.m) * sizeof(double), stream>>>(a);
+  gsp_tile_kernel<T><<<dim3(8 * ((a.N + 7) / 8) * a.n_pairs), 256, 0, stream>>>(a);
+  rcr_mean_kernel<T><<<dim3((a.d + 63) / 64), 256, 0, stream>>>(a);
+  rcr_hidden_kernel<T><<<dim3(a.N * (a.m / (4 * kHRows))), 256, 0, stream>>>(a);
+  rcr_out_kernel<T><<<dim3(a.N * (a.d / (4 * kFRows))), 256, 0, stream>>>(a);
+  tables_expert_kernel<<<dim3(a.N), 256, 0, stream>>>(a);
   tables_finalize_kernel<<<1, 256, 0, stream>>>(a);
 }
 
 size_t al(size_t v) { return (v + 255) / 256 * 256; }
 
+// workspace regions of TabArgs, in order; returns the bytes used
+size_t carve(TabArgs &a, char *ws) {
+  size_t off = 0;
+  auto take = [&](size_t n) {
+    double *p = reinterpret_cast<double *>(ws + off);
+    off += al(n * sizeof(double));
+    return p;
+  };
+  const size_t N = a.N, d = a.d, m = a.m;
+  a.pair_part = take(N * a.n_pairs * 2);
+  a.wbar = take(d);
+  a.h = take(N * m);
+  a.row_norm2 = take(N * m * 2);
+  a.f_part = take(N * (d / (4 * kFRows)));
+  a.q_norm = take(N);
+  a.gsp_raw = take(N);
+  a.rcr_raw = take(N);
+  return off;
+}
+
+void set_shape(TabArgs &a, int N, int d, int m) {
+  a.N = N;
+  a.d = d;
+  a.m = m;
+  a.mt = m / 64;
+  a.n_pairs = a.mt * (a.mt + 1) / 2;
+}
+
 }  // namespace
 
 size_t tables_workspace_bytes(int N, int d, int m) {
-  const size_t mt = static_cast<size_t>(m) / 64, np = mt * (mt + 1) / 2;
-  return al(static_cast<size_t>(N) * np * 2 * 8) + al(static_cast<size_t>(d) * 8) + 3 * al(static_cast<size_t>(N) * 2 * 8);
+  TabArgs a{};
+  set_shape(a, N, d, m);
+  return carve(a, nullptr);
 }
 
 hipError_t launch_tables(const TablesCall &c, hipStream_t stream) {
   TabArgs a{};
+  set_shape(a, c.N, c.d, c.m);
+  carve(a, static_cast<char *>(c.workspace));
   a.gamma = c.gamma;
   a.w_router = c.w_router;
   a.w_gate = c.w_gate;
   a.w_up = c.w_up;
   a.w_down = c.w_down;
-  a.N = c.N;
-  a.d = c.d;
-  a.m = c.m;
-  a.mt = c.m / 64;
-  a.n_pairs = a.mt * (a.mt + 1) / 2;
   a.eps = c.eps;
   a.rho = 1.0;
-  char *ws = static_cast<char *>(c.workspace);
-  a.pair_part = reinterpret_cast<double *>(ws);
-  ws += al(static_cast<size_t>(c.N) * a.n_pairs * 2 * 8);
-  a.wbar = reinterpret_cast<double *>(ws);
-  ws += al(static_cast<size_t>(c.d) * 8);
-  a.rcr_raw = reinterpret_cast<double *>(ws);
-  ws += al(static_cast<size_t>(c.N) * 2 * 8);
-  a.norm2 = reinterpret_cast<double *>(ws);
-  ws += al(static_cast<size_t>(c.N) * 2 * 8);
-  a.gsp_raw = reinterpret_cast<double *>(ws);
   a.a_gsp = c.a_gsp;
   a.a_rcr = c.a_rcr;
   a.a_gsp64 = c.a_gsp64;

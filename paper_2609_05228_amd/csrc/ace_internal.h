@@ -55,6 +55,7 @@ __device__ __forceinline__ float silu_for_bf16(float v) {
 constexpr int kMaxN = 256;   // routed experts supported by the router kernel
 constexpr int kMaxK = 8;     // top-k supported by the router kernel
 constexpr int kTileM = 256;  // rows of one grouped-GEMM M tile (the dispatch plan's tile size)
+constexpr int kTileMF32 = 64;  // ... of an fp32 layer past the small batches (see expert_gemm.hip)
 constexpr int kRouteTokens = 16;  // tokens per router workgroup (one dispatch-plan chunk)
 constexpr int kRouteMaxSlices = 16;  // K slices of the small-batch router
 constexpr int kRoutePairMinChunks = 256;  // bf16 batches of more chunks: one router workgroup per chunk pair
@@ -113,12 +114,13 @@ struct PlanArgs {
   int32_t *n_tiles;                  // [1]
   int32_t *tile_order;               // [max_tiles] or null: the gate/up launch's tile order (see plan_kernel)
   int T, k, N, G;
+  int tile_m;                        // rows of an M tile
 };
 
 // Grouped GEMM over the dispatch plan.  Tile g covers rows tile_row0[g] ..
 // tile_row0[g] + tile_rows[g] - 1 of the compacted slot order, all routed to
 // expert tile_expert[g].  In dense mode (dense_rows > 0) tile g covers rows
-// g*kTileM .. of a single group with identity row->token map and expert 0.
+// g*tile .. of a single group (tile: kTileM, or kTileMF32 in fp32) with identity row->token map and expert 0.
 struct GemmArgs {
   const void *act;        // gate/up: xn [T, d] (gathered through perm); down: H [rows, m]
   const int32_t *perm;    // row -> token (gate/up, routed); null in dense mode / for down
@@ -130,8 +132,8 @@ struct GemmArgs {
   int dense_rows;         // > 0: dense single-group mode with this many rows
   int max_groups;         // upper bound of M tiles (grid sizing)
   int d, m;               // hidden and intermediate sizes of this GEMM's expert(s)
-  // A dense expert appended to the routed tiles (bf16 grouped GEMM): tiles
-  // n_tiles[0] .. n_tiles[0] + sh_tiles - 1 cover its rows (t - n_tiles[0]) * kTileM ..
+  // A dense expert appended to the routed tiles (grouped GEMM): tiles
+  // n_tiles[0] .. n_tiles[0] + sh_tiles - 1 cover its rows (t - n_tiles[0]) * tile ..
   // with the identity row map, its own operands and its own output.  0: none.
   int sh_tiles, sh_rows;
   const void *sh_act, *sh_w0, *sh_w1;
@@ -142,10 +144,9 @@ struct GemmArgs {
 // `splits` parts when the batch is too small to fill the GPU otherwise.
 struct SkinnyArgs {
   GemmArgs g;
-  int splits;      // K splits (1: write H / Y in bf16 directly)
+  int splits;      // K splits: 1, 2, 4 or 8 (down: 1 writes Y, else partial sums)
   int rows_cap;    // row capacity of a partial-sum plane (T * k)
-  float *part0;    // gate/up: gate partials [splits, rows_cap, m]; down: Y partials [splits, rows_cap, d]
-  float *part1;    // gate/up: up partials [splits, rows_cap, m]
+  float *part;     // down with several splits: Y partials [splits, rows_cap, d]
   // self_plan (routed gate/up, 2-4 router chunks): each wave derives its tile (the
   // grp-th expert with kept slots) and the tokens of its rows from the router's
   // per-chunk counts and the routing, instead of reading a plan; one item per
@@ -179,11 +180,10 @@ hipError_t launch_plan(const PlanArgs &a, hipStream_t stream);
 hipError_t launch_gateup(const GemmArgs &a, bool bf16, hipStream_t stream);
 hipError_t launch_down(const GemmArgs &a, bool bf16, hipStream_t stream);
 hipError_t launch_combine(const CombineArgs &a, bool bf16, hipStream_t stream);
-// gate/up (gateup = true; reduces K-split partials into H when splits > 1, with
-// n_rows = device count of rows in routed mode) or down
 // whether launch_plan writes PlanArgs::tile_order for these sizes (the one-kernel plan)
 bool plan_writes_order(const PlanArgs &a);
-hipError_t launch_skinny(const SkinnyArgs &a, bool gateup, const int32_t *n_rows, hipStream_t stream);
+// gate/up (gateup = true) or down of a small batch
+hipError_t launch_skinny(const SkinnyArgs &sa, bool gateup, bool bf16, hipStream_t stream);
 
 // Offline GSP / RCR tables (Alg. 2, Alg. 3) in fp64
 struct TablesCall {

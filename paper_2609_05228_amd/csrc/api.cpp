@@ -39,14 +39,14 @@ int pick_splits(long items, int K) {
 
 struct Layout {
   size_t xn, zpart, sspart, local_rank, chunk_count, chunk_base, slot_row, gates, counts, offsets, perm;
-  size_t tile_e, tile_r0, tile_rows, tile_ord, n_tiles, H, Y, Hs, Ys, part_g, part_u, part_y, total;
-  int G, max_groups, dense_groups;
-  bool skinny;          // small-batch path (bf16, T <= kSkinnyMaxT)
+  size_t tile_e, tile_r0, tile_rows, tile_ord, n_tiles, H, Y, Hs, Ys, part_y, total;
+  int G, tile_m, max_groups, dense_groups;
+  bool skinny;          // small-batch path (T <= kSkinnyMaxT)
   int splits_gu, splits_dn;
   int ksplit, zstride;  // router K slices (0: fused) and partial-logit row stride
 };
 
-Layout layout_for(const ace_moe_desc &d) {
+Layout layout_of(const ace_moe_desc &d, bool split_down) {
   Layout L{};
   const size_t T = static_cast<size_t>(d.T), dd = static_cast<size_t>(d.d);
   const size_t N = static_cast<size_t>(d.N), k = static_cast<size_t>(d.k), m = static_cast<size_t>(d.m);
@@ -61,15 +61,16 @@ Layout layout_for(const ace_moe_desc &d) {
     while (L.ksplit < ace::kRouteMaxSlices && nb % (2 * L.ksplit) == 0 && L.G * L.ksplit < 128) L.ksplit *= 2;
   }
   L.zstride = 16 * ace::route_expert_tiles(d.N);
-  L.skinny = d.dtype == ACE_BF16 && d.T <= kSkinnyMaxT;
+  L.skinny = d.T <= kSkinnyMaxT;
   L.splits_gu = L.splits_dn = 1;
   if (L.skinny) {
     const long tiles = static_cast<long>(slots < N ? slots : N);
     L.splits_gu = pick_splits(tiles * (d.m / 16), d.d);
-    L.splits_dn = pick_splits(tiles * (d.d / 32), d.m);
+    if (split_down) L.splits_dn = pick_splits(tiles * (d.d / 32), d.m);
   }
-  L.max_groups = static_cast<int>((slots + ace::kTileM - 1) / ace::kTileM + (slots < N ? slots : N));
-  L.dense_groups = static_cast<int>((T + ace::kTileM - 1) / ace::kTileM);
+  L.tile_m = d.dtype == ACE_F32 && !L.skinny ? ace::kTileMF32 : ace::kTileM;
+  L.max_groups = static_cast<int>((slots + L.tile_m - 1) / L.tile_m + (slots < N ? slots : N));
+  L.dense_groups = static_cast<int>((T + L.tile_m - 1) / L.tile_m);
   size_t off = 0;
   auto take = [&](size_t bytes) {
     const size_t o = off;
@@ -98,13 +99,16 @@ Layout layout_for(const ace_moe_desc &d) {
     L.Hs = take(T * static_cast<size_t>(d.m_shared) * esz);
     L.Ys = take(T * dd * esz);
   }
-  if (L.splits_gu > 1) {
-    L.part_g = take(static_cast<size_t>(L.splits_gu) * slots * m * 4);
-    L.part_u = take(static_cast<size_t>(L.splits_gu) * slots * m * 4);
-  }
   if (L.splits_dn > 1) L.part_y = take(static_cast<size_t>(L.splits_dn) * slots * dd * 4);
   L.total = off;
   return L;
+}
+
+// An fp32 layer whose partial sums of the K-split down GEMM would not fit the static
+// scratch goes without the split, so that what fits it without them still does.
+Layout layout_for(const ace_moe_desc &d) {
+  const Layout L = layout_of(d, true);
+  return d.dtype == ACE_F32 && L.splits_dn > 1 && L.total > ACE_NOALLOC_SCRATCH_BYTES ? layout_of(d, false) : L;
 }
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -492,8 +496,9 @@ ace_status forward_impl(const ace_moe_desc *desc, const void *x, const ace_moe_w
   pa.k = d.k;
   pa.N = d.N;
   pa.G = L.G;
+  pa.tile_m = L.tile_m;
   // one chunk: the router's select workgroup already wrote the plan; several chunks of a
-  // small bf16 batch: the skinny gate/up kernel derives it (SkinnyArgs::self_plan)
+  // small batch: the skinny gate/up kernel derives it (SkinnyArgs::self_plan)
   const bool self_plan = L.skinny && L.G > 1;
   const bool planned = (L.ksplit > 0 && L.G == 1) || self_plan;
   if (!planned && ace::launch_plan(pa, stream) != hipSuccess) return ACE_ERR_HIP;
@@ -524,7 +529,7 @@ ace_status forward_impl(const ace_moe_desc *desc, const void *x, const ace_moe_w
   gd.out = at(L.Y);
   // a shared expert with the routed experts' intermediate size runs as extra M tiles
   // of the routed grouped GEMMs (one launch each instead of two half-filled ones)
-  const bool shared_in_routed = d.n_shared == 1 && bf16 && !L.skinny && d.m_shared == d.m;
+  const bool shared_in_routed = d.n_shared == 1 && !L.skinny && d.m_shared == d.m;
   if (shared_in_routed) {
     const int st = L.dense_groups;
     g.sh_tiles = gd.sh_tiles = st;
@@ -542,7 +547,7 @@ ace_status forward_impl(const ace_moe_desc *desc, const void *x, const ace_moe_w
   }
   if (L.skinny) {
     const int slots = d.T * d.k;
-    ace::SkinnyArgs su{g, L.splits_gu, slots, static_cast<float *>(at(L.part_g)), static_cast<float *>(at(L.part_u))};
+    ace::SkinnyArgs su{g, L.splits_gu, slots, nullptr};
     if (self_plan) {
       su.self_plan = true;
       su.topk_idx = out->topk_idx;
@@ -561,10 +566,10 @@ ace_status forward_impl(const ace_moe_desc *desc, const void *x, const ace_moe_w
       su.N = d.N;
       su.G = L.G;
     }
-    if (ace::launch_skinny(su, true, offsets + d.N, stream) != hipSuccess) return ACE_ERR_HIP;
+    if (ace::launch_skinny(su, true, bf16, stream) != hipSuccess) return ACE_ERR_HIP;
     mark(prof, 3, stream);
-    ace::SkinnyArgs sd{gd, L.splits_dn, slots, static_cast<float *>(at(L.part_y)), nullptr};
-    if (ace::launch_skinny(sd, false, offsets + d.N, stream) != hipSuccess) return ACE_ERR_HIP;
+    ace::SkinnyArgs sd{gd, L.splits_dn, slots, static_cast<float *>(at(L.part_y))};
+    if (ace::launch_skinny(sd, false, bf16, stream) != hipSuccess) return ACE_ERR_HIP;
   } else {
     if (ace::launch_gateup(g, bf16, stream) != hipSuccess) return ACE_ERR_HIP;
     mark(prof, 3, stream);
@@ -590,10 +595,10 @@ ace_status forward_impl(const ace_moe_desc *desc, const void *x, const ace_moe_w
     sd.w1 = nullptr;
     sd.out = at(L.Ys);
     if (L.skinny) {
-      ace::SkinnyArgs su{s, 1, d.T, nullptr, nullptr};
-      ace::SkinnyArgs sdn{sd, 1, d.T, nullptr, nullptr};
-      if (ace::launch_skinny(su, true, nullptr, stream) != hipSuccess) return ACE_ERR_HIP;
-      if (ace::launch_skinny(sdn, false, nullptr, stream) != hipSuccess) return ACE_ERR_HIP;
+      ace::SkinnyArgs su{s, 1, d.T, nullptr};
+      ace::SkinnyArgs sdn{sd, 1, d.T, nullptr};
+      if (ace::launch_skinny(su, true, bf16, stream) != hipSuccess) return ACE_ERR_HIP;
+      if (ace::launch_skinny(sdn, false, bf16, stream) != hipSuccess) return ACE_ERR_HIP;
     } else {
       if (ace::launch_gateup(s, bf16, stream) != hipSuccess) return ACE_ERR_HIP;
       if (ace::launch_down(sd, bf16, stream) != hipSuccess) return ACE_ERR_HIP;

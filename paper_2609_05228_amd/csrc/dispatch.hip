@@ -96,7 +96,7 @@ __global__ __launch_bounds__(128) void scatter_kernel(PlanArgs a) {
   const int g = blockIdx.x;
   for (int e = tid; e < N; e += 128) {
     cnt[e] = a.counts[e];
-    tcnt[e] = (cnt[e] + kTileM - 1) / kTileM;
+    tcnt[e] = (cnt[e] + a.tile_m - 1) / a.tile_m;
   }
   __syncthreads();
   if (tid < 64) {
@@ -112,8 +112,8 @@ __global__ __launch_bounds__(128) void scatter_kernel(PlanArgs a) {
       for (int j = 0; j < tcnt[e]; ++j) {
         const int tg = toff[e] + j;
         a.tile_expert[tg] = e;
-        a.tile_row0[tg] = off[e] + j * kTileM;
-        a.tile_rows[tg] = min(kTileM, cnt[e] - j * kTileM);
+        a.tile_row0[tg] = off[e] + j * a.tile_m;
+        a.tile_rows[tg] = min(a.tile_m, cnt[e] - j * a.tile_m);
       }
     }
   }
@@ -216,7 +216,7 @@ __global__ __launch_bounds__(256) void plan_kernel(PlanArgs a) {
       p += (red[q + 2][rr * NW + wi] >> sh) & 0xffffu;
     }
     cnt[tid] = t;
-    tcnt[tid] = (t + kTileM - 1) / kTileM;
+    tcnt[tid] = (t + a.tile_m - 1) / a.tile_m;
     base[tid] = p;
   }
   __syncthreads();
@@ -231,8 +231,8 @@ __global__ __launch_bounds__(256) void plan_kernel(PlanArgs a) {
       for (int j = 0; j < tcnt[e]; ++j) {
         const int tg = toff[e] + j;
         a.tile_expert[tg] = e;
-        a.tile_row0[tg] = off[e] + j * kTileM;
-        a.tile_rows[tg] = min(kTileM, cnt[e] - j * kTileM);
+        a.tile_row0[tg] = off[e] + j * a.tile_m;
+        a.tile_rows[tg] = min(a.tile_m, cnt[e] - j * a.tile_m);
       }
     }
     for (int e = tid; e <= N; e += 256) a.offsets[e] = off[e];

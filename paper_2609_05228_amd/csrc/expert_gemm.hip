@@ -34,8 +34,16 @@
 //    the same 16 features, so SwiGLU happens in registers; down: 32 columns);
 //  * the down launch gives each workgroup two N tiles of one M tile, run as one
 //    pipeline (the second tile's first stages load under the first's last steps).
-// fp32 path: fp32 MFMA (v_mfma_f32_16x16x4f32) on LDS-staged operands (small
-// parity workloads).
+// fp32 path: the same tile body on 32-wide K stages, four v_mfma_f32_16x16x4f32 per
+// pair of fragments.  An fp32 multiply takes 16 times the matrix time per byte, so
+// the matrix cores bound all but the shortest tiles, and what counts is to spread
+// the work evenly: M tiles of 64 rows (the plan's tile size for fp32 layers), 32
+// features or 64 columns wide, half the LDS each, so two workgroups share a CU and
+// one's ramp and stores run under the other's K loop.  The kernels that loaded one
+// 16-wide K step at a time between barriers took 199 + 105 us for 517 tokens (1024
+// hidden, 32 experts of 512, top-4), 256-row tiles with all of the LDS 63 + 35, half
+// of it 53 + 29; 929 tokens on 11 experts take 159 us a layer with 256-row tiles,
+// 120 with 64-row ones.  Tiles twice as wide leave CUs idle (929 tokens: 270 us).
 //
 // Launch order is XCD-aware: workgroups are dealt to the 8 XCDs round-robin, so
 // block b runs on XCD b % 8; the N tiles of one M tile are mapped to one XCD so
@@ -48,7 +56,6 @@ namespace ace {
 namespace {
 
 constexpr int kFragBytes = kUnitBytes;  // one staged unit (8 rows x 64 bf16, or 16 rows x 32)
-constexpr int kLdsBytes = kPipeLdsBytes;
 static_assert(kFragBytes == kPipeUnitBytes, "one DMA unit per fragment");
 
 struct TileInfo {
@@ -65,15 +72,16 @@ __device__ __forceinline__ void map_block(int b, int nN, int *grp, int *nt) {
   *nt = j % nN;
 }
 
-__device__ __forceinline__ TileInfo tile_info(const GemmArgs &a, int grp) {
+// TM: rows of an M tile
+template <int TM> __device__ __forceinline__ TileInfo tile_info(const GemmArgs &a, int grp) {
   TileInfo ti;
   ti.sh = false;
   if (a.dense_rows > 0) {
     ti.e = 0;
-    ti.row0 = grp * kTileM;
-    ti.rows = min(kTileM, a.dense_rows - ti.row0);
+    ti.row0 = grp * TM;
+    ti.rows = min(TM, a.dense_rows - ti.row0);
     ti.valid = ti.rows > 0;
-    ti.once = a.dense_rows <= kTileM;
+    ti.once = a.dense_rows <= TM;
   } else {
     const int nr = a.n_tiles[0];
     if (a.tile_order && grp < nr) grp = a.tile_order[grp];
@@ -87,17 +95,14 @@ __device__ __forceinline__ TileInfo tile_info(const GemmArgs &a, int grp) {
     if (!ti.valid && grp - nr < a.sh_tiles) {
       ti.sh = true;
       ti.e = 0;
-      ti.row0 = (grp - nr) * kTileM;
-      ti.rows = min(kTileM, a.sh_rows - ti.row0);
+      ti.row0 = (grp - nr) * TM;
+      ti.rows = min(TM, a.sh_rows - ti.row0);
       ti.valid = ti.rows > 0;
       ti.once = a.sh_tiles == 1;
     }
   }
   return ti;
 }
-
-__device__ __forceinline__ float silu(float v) { return v / (1.0f + expf(-v)); }  // fp32 layers
-
 
 constexpr int kGemmWaves = 8;  // waves per workgroup (two per SIMD)
 // 32-wide k halves per pipeline stage.  Two (64-wide stages) measured faster than
@@ -108,14 +113,14 @@ template <int CG> constexpr int stage_halves() { return 2; }
 // the exact wait counts of a wave's DMA issue sequence.
 
 // Output stores of gemm_tile: lane holds column r16 of each block, rows 4*g + q.
-template <bool GATEUP, int MW, int CW, int RW, int BN>
+template <typename T, bool GATEUP, int MW, int CW, int RW, int BN>
 __device__ __forceinline__ void store_tile_impl(const GemmArgs &a, const TileInfo &ti, void *outp,
                                                 f32x4_t (&acc)[MW][2 * CW], int nt, int wr, int wc, int r16, int g) {
 #pragma unroll
   for (int fl = 0; fl < CW; ++fl) {
     const int grp = wc * CW + fl;
     if (GATEUP) {
-      bf16_t *H = static_cast<bf16_t *>(outp);
+      T *H = static_cast<T *>(outp);
       const int f = nt * BN + grp * 16 + r16;
 #pragma unroll
       for (int i = 0; i < MW; ++i)
@@ -123,11 +128,10 @@ __device__ __forceinline__ void store_tile_impl(const GemmArgs &a, const TileInf
         for (int q = 0; q < 4; ++q) {
           const int row = (wr + RW * i) * 16 + 4 * g + q;
           if (row < ti.rows)
-            H[static_cast<size_t>(ti.row0 + row) * a.m + f] =
-                f32_to_bf16(silu_for_bf16(acc[i][fl * 2][q]) * acc[i][fl * 2 + 1][q]);
+            H[static_cast<size_t>(ti.row0 + row) * a.m + f] = swiglu(acc[i][fl * 2][q], acc[i][fl * 2 + 1][q], T{});
         }
     } else {
-      bf16_t *Y = static_cast<bf16_t *>(outp);
+      T *Y = static_cast<T *>(outp);
       const int n = nt * BN + grp * 32 + r16;
 #pragma unroll
       for (int i = 0; i < MW; ++i)
@@ -135,9 +139,9 @@ __device__ __forceinline__ void store_tile_impl(const GemmArgs &a, const TileInf
         for (int q = 0; q < 4; ++q) {
           const int row = (wr + RW * i) * 16 + 4 * g + q;
           if (row < ti.rows) {
-            bf16_t *yr = Y + static_cast<size_t>(ti.row0 + row) * a.d + n;
-            yr[0] = f32_to_bf16(acc[i][fl * 2][q]);
-            yr[16] = f32_to_bf16(acc[i][fl * 2 + 1][q]);
+            T *yr = Y + static_cast<size_t>(ti.row0 + row) * a.d + n;
+            yr[0] = Elem<T>::from_f32(acc[i][fl * 2][q]);
+            yr[16] = Elem<T>::from_f32(acc[i][fl * 2 + 1][q]);
           }
         }
     }
@@ -157,13 +161,14 @@ __device__ __forceinline__ void store_tile_impl(const GemmArgs &a, const TileInf
 // c ^ r (both units of a block alike), so the MFMA fragment reads (16 rows, one
 // chunk each) run at the full LDS rate.  Wave w computes row blocks wr, wr+RW,
 // ... (wr = w/2) against the CG/2 column groups starting at wc*CG/2 (wc = w%2).
-template <bool GATEUP, int MB, int CG, int KH, int W>
+template <typename T, bool GATEUP, int MB, int CG, int KH, int W>
 __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const TileInfo &ti, int nt0, int ntiles, int erot,
                                           uint8_t *smem) {
   static_assert(KH == 2, "8-row DMA units span a 64-wide K stage");
   using P = Pipe<MB, CG, KH, W>;
   constexpr int RW = W / 2;    // waves along the rows
-  constexpr int NAM = P::NA_MAX, NB = P::NB, SA = P::SA, SB = P::SB, BK = P::BK;
+  constexpr int NAM = P::NA_MAX, NB = P::NB, SA = P::SA, SB = P::SB, BK = kStageElems<T>;
+  typedef typename Frag<T>::type frag_t;
   constexpr int MW = MB / RW;  // row blocks per wave
   constexpr int CW = CG / 2;   // column groups per wave
   constexpr int BN = GATEUP ? 16 * CG : 32 * CG;  // tile width (features or output columns)
@@ -174,7 +179,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const TileInfo &ti,
   const int wr = wave >> 1, wc = wave & 1;
   const int K = GATEUP ? a.d : a.m;
   // routed tile: the routed experts' operands; appended dense-expert tile: its own
-  const bf16_t *act = static_cast<const bf16_t *>(ti.sh ? a.sh_act : a.act);
+  const T *act = static_cast<const T *>(ti.sh ? a.sh_act : a.act);
   const int32_t *perm = ti.sh ? nullptr : a.perm;
   const void *w0 = ti.sh ? a.sh_w0 : a.w0;
   const void *w1 = ti.sh ? a.sh_w1 : a.w1;
@@ -200,19 +205,19 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const TileInfo &ti,
     srow[j] = perm ? gload_i32(perm + ti.row0 + row) : ti.row0 + row;
   }
   // B units this wave stages: b = wave * NB + t -> block b / 2, row half t % 2
-  const bf16_t *bsrc[NB];
+  const T *bsrc[NB];
 #pragma unroll
   for (int t = 0; t < NB; ++t) {
     const int b = wave * NB + t;
     const int blk = b >> 1, j = b & 1;
     const int fg = blk >> 1, cb = blk & 1;
-    const int c = 8 * unit_chunk(lane);
+    const int c = kChunkElems<T> * unit_chunk(lane);
     if (GATEUP) {
       const size_t f = static_cast<size_t>(ti.e) * a.m + nt0 * BN + fg * 16 + 8 * j + ur;
-      bsrc[t] = static_cast<const bf16_t *>(cb ? w1 : w0) + f * a.d + c;
+      bsrc[t] = static_cast<const T *>(cb ? w1 : w0) + f * a.d + c;
     } else {
       const size_t n = static_cast<size_t>(ti.e) * a.d + nt0 * BN + fg * 32 + cb * 16 + 8 * j + ur;
-      bsrc[t] = static_cast<const bf16_t *>(w0) + n * a.m + c;
+      bsrc[t] = static_cast<const T *>(w0) + n * a.m + c;
     }
   }
   // fragment read offsets inside a 16-row block (two units) for k halves 0 and 1
@@ -228,7 +233,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const TileInfo &ti,
 #pragma unroll
     for (int c = 0; c < 2 * CW; ++c) acc[i][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   auto store_tile = [&](f32x4_t (&ac)[MW][2 * CW], int nt) {
-    store_tile_impl<GATEUP, MW, CW, RW, BN>(a, ti, outp, ac, nt, wr, wc, r16, g);
+    store_tile_impl<T, GATEUP, MW, CW, RW, BN>(a, ti, outp, ac, nt, wr, wc, r16, g);
   };
 
   const int nk = K / BK;
@@ -279,9 +284,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const TileInfo &ti,
 #pragma unroll
     for (int j = 0; j < NAM; ++j) reg_ready(srow[j]);
   }
-  const bf16_t *asrc[NAM];
+  const T *asrc[NAM];
 #pragma unroll
-  for (int j = 0; j < NAM; ++j) asrc[j] = act + static_cast<size_t>(srow[j]) * K + 8 * unit_chunk(lane);
+  for (int j = 0; j < NAM; ++j) asrc[j] = act + static_cast<size_t>(srow[j]) * K + kChunkElems<T> * unit_chunk(lane);
   for (int s = 0; s < SA - 1 && s < NK; ++s) {
     const uint32_t st = ldsA + s * P::ASZ;
 #pragma unroll
@@ -291,13 +296,13 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const TileInfo &ti,
 
   using CF = Closed<P>;
   for (int kt = 0; kt < NK; ++kt) {
-    if (CF::on && na > 0) {
+    if constexpr (CF::on) {  // bodies for more than 64 rows: every wave stages A units
       if (CF::nb_pending(kt, NK))
         wait_vmcnt(NB);
       else
         wait_vmcnt(0);
     } else {
-      wait_vmcnt(pending_ok<P>(kt, NK, na));
+      wait_vmcnt_in<0, Pending<P>::MAX>(Pending<P>::count(kt, NK, na));
     }
     barrier();  // stage kt landed for every wave; every wave is done with stage kt-1
     if (kt + SA - 1 < NK) {
@@ -311,19 +316,19 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const TileInfo &ti,
     const uint8_t *sb = smemB + (kt % SB) * P::BSZ;
 #pragma unroll
     for (int h = 0; h < KH; ++h) {
-      bf16x8_t bf[2 * CW];  // [fl * 2 + cb]: column group wc*CW + fl, block cb
+      frag_t bf[2 * CW];  // [fl * 2 + cb]: column group wc*CW + fl, block cb
 #pragma unroll
       for (int c = 0; c < 2 * CW; ++c)
-        bf[c] = *reinterpret_cast<const bf16x8_t *>(sb + (2 * (wc * CW + (c >> 1)) + (c & 1)) * 2 * kFragBytes +
+        bf[c] = *reinterpret_cast<const frag_t *>(sb + (2 * (wc * CW + (c >> 1)) + (c & 1)) * 2 * kFragBytes +
                                                     (h ? rd_off1 : rd_off0));
       // every row block's fragment is read up front, with the weight fragments
       // (blocks past the tile read stale LDS and are not multiplied): a read
       // placed after the branch below made each row block's MFMAs wait a full
       // LDS round trip
-      bf16x8_t av[MW];
+      frag_t av[MW];
 #pragma unroll
       for (int i = 0; i < MW; ++i)
-        av[i] = *reinterpret_cast<const bf16x8_t *>(sa + (wr + RW * i) * 2 * kFragBytes + (h ? rd_off1 : rd_off0));
+        av[i] = *reinterpret_cast<const frag_t *>(sa + (wr + RW * i) * 2 * kFragBytes + (h ? rd_off1 : rd_off0));
       // an empty use here keeps the compiler from sinking each read into the
       // branch that multiplies it
 #pragma unroll
@@ -332,8 +337,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const TileInfo &ti,
       for (int i = 0; i < MW; ++i) {
         if ((wr + RW * i) * 16 >= ti.rows) break;  // wave-uniform: row blocks past the tile
 #pragma unroll
-        for (int c = 0; c < 2 * CW; ++c)
-          acc[i][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[i], bf[c], acc[i][c], 0, 0, 0);
+        for (int j = 0; j < Frag<T>::steps; ++j)
+#pragma unroll
+          for (int c = 0; c < 2 * CW; ++c) acc[i][c] = Frag<T>::mma(av[i], bf[c], j, acc[i][c]);
       }
       // the weight DMAs of stage kt + SB - 1 go out behind the first k half's
       // MFMAs, so their issue (the memory pipeline's back-pressure) overlaps the
@@ -360,146 +366,32 @@ template <bool GATEUP> constexpr int tile_width(int cg) { return GATEUP ? 16 * c
 
 // TPW (1 or 2): N tiles per workgroup, consecutive tiles of one M tile in one
 // pipeline (gemm_tile).
-template <bool GATEUP, int CG, int W, int TPW>
-__global__ __launch_bounds__(W * 64) void grouped_gemm_bf16_kernel(GemmArgs a) {
+template <typename T, bool GATEUP, int CG, int W, int TPW>
+__global__ __launch_bounds__(W * 64) void grouped_gemm_kernel(GemmArgs a) {
   static_assert(TPW == 1 || TPW == 2, "one or two N tiles per workgroup");
   const int nN = (GATEUP ? a.m : a.d) / tile_width<GATEUP>(CG);
   const int nP = (nN + TPW - 1) / TPW;
   int grp, np;
   map_block(blockIdx.x, nP, &grp, &np);
   const int nt0 = np * TPW, ntiles = min(TPW, nN - nt0);
-  const TileInfo ti = tile_info(a, grp);
+  const TileInfo ti = tile_info<sizeof(T) == 4 ? kTileMF32 : kTileM>(a, grp);
   if (!ti.valid) return;
-  __shared__ __align__(16) uint8_t smem[kLdsBytes];
-  const int blocks = (ti.rows + 15) >> 4;
+  __shared__ __align__(16) uint8_t smem[Pipe<16, CG, stage_halves<CG>(), W>::LDS];
+  [[maybe_unused]] const int blocks = (ti.rows + 15) >> 4;
   // K rotation key: the expert (the appended dense expert gets its own)
   const int erot = ti.sh ? 0x155 : ti.e;
-  if (blocks <= 4)
-    gemm_tile<GATEUP, 4, CG, stage_halves<CG>(), W>(a, ti, nt0, ntiles, erot, smem);
-  else if (blocks <= 8)
-    gemm_tile<GATEUP, 8, CG, stage_halves<CG>(), W>(a, ti, nt0, ntiles, erot, smem);
-  else if (blocks <= 12)
-    gemm_tile<GATEUP, 12, CG, stage_halves<CG>(), W>(a, ti, nt0, ntiles, erot, smem);
-  else
-    gemm_tile<GATEUP, 16, CG, stage_halves<CG>(), W>(a, ti, nt0, ntiles, erot, smem);
-}
-
-// ------------------------------------------------------------------ fp32 (MFMA)
-// fp32 layers (the small parity workloads): v_mfma_f32_16x16x4f32 on fp32
-// operands staged in LDS 16 k at a time.  A workgroup (4 waves) takes one M tile
-// (up to 256 rows) and one N tile of 16 features (gate/up: a gate block and an
-// up block) or 16 output columns (down); wave w multiplies row blocks w, w+4,
-// w+8, w+12.  Operand lanes: A row l%16 / B column l%16, k = l/16 of the
-// instruction's 4.
-constexpr int F_BN = 16;
-constexpr int F_BK = 16;
-
-__global__ __launch_bounds__(256) void gateup_f32_kernel(GemmArgs a) {
-  const int nN = a.m / F_BN;
-  int grp, nt;
-  map_block(blockIdx.x, nN, &grp, &nt);
-  const TileInfo ti = tile_info(a, grp);
-  if (!ti.valid) return;
-  __shared__ float As[kTileM][F_BK + 1];
-  __shared__ float Bg[F_BN][F_BK + 1];
-  __shared__ float Bu[F_BN][F_BK + 1];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r16 = lane & 15, g = lane >> 4;
-  const int d = a.d, m = a.m, f0 = nt * F_BN;
-  const int nrb = (ti.rows + 15) >> 4;
-  const float *xn = static_cast<const float *>(a.act);
-  const float *wg = static_cast<const float *>(a.w0);
-  const float *wu = static_cast<const float *>(a.w1);
-  f32x4_t accg[4], accu[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) accg[i] = accu[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < d; k0 += F_BK) {
-    for (int c = tid; c < kTileM * F_BK; c += 256) {
-      const int r = c >> 4, kk = c & 15;
-      float v = 0.f;
-      if (r < ti.rows) {
-        const int tok = a.perm ? a.perm[ti.row0 + r] : ti.row0 + r;
-        v = xn[static_cast<size_t>(tok) * d + k0 + kk];
-      }
-      As[r][kk] = v;
-    }
-    {
-      const int r = tid >> 4, kk = tid & 15;
-      const size_t wrow = (static_cast<size_t>(ti.e) * m + f0 + r) * d + k0 + kk;
-      Bg[r][kk] = wg[wrow];
-      Bu[r][kk] = wu[wrow];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < F_BK / 4; ++j) {
-      const float bgv = Bg[r16][4 * j + g], buv = Bu[r16][4 * j + g];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int rb = wave + 4 * i;
-        if (rb >= nrb) break;  // wave-uniform
-        const float av = As[rb * 16 + r16][4 * j + g];
-        accg[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bgv, accg[i], 0, 0, 0);
-        accu[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, buv, accu[i], 0, 0, 0);
-      }
-    }
-    __syncthreads();
+  if constexpr (sizeof(T) == 4) {  // tiles of at most 64 rows
+    gemm_tile<T, GATEUP, kTileMF32 / 16, CG, stage_halves<CG>(), W>(a, ti, nt0, ntiles, erot, smem);
+  } else {
+    if (blocks <= 4)
+      gemm_tile<T, GATEUP, 4, CG, stage_halves<CG>(), W>(a, ti, nt0, ntiles, erot, smem);
+    else if (blocks <= 8)
+      gemm_tile<T, GATEUP, 8, CG, stage_halves<CG>(), W>(a, ti, nt0, ntiles, erot, smem);
+    else if (blocks <= 12)
+      gemm_tile<T, GATEUP, 12, CG, stage_halves<CG>(), W>(a, ti, nt0, ntiles, erot, smem);
+    else
+      gemm_tile<T, GATEUP, 16, CG, stage_halves<CG>(), W>(a, ti, nt0, ntiles, erot, smem);
   }
-  // lane holds feature f0 + r16 of rows 16 rb + 4 g + q
-  float *H = static_cast<float *>(a.out);
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int r = (wave + 4 * i) * 16 + 4 * g + q;
-      if (r < ti.rows) H[static_cast<size_t>(ti.row0 + r) * m + f0 + r16] = silu(accg[i][q]) * accu[i][q];
-    }
-}
-
-__global__ __launch_bounds__(256) void down_f32_kernel(GemmArgs a) {
-  const int nN = a.d / F_BN;
-  int grp, nt;
-  map_block(blockIdx.x, nN, &grp, &nt);
-  const TileInfo ti = tile_info(a, grp);
-  if (!ti.valid) return;
-  __shared__ float As[kTileM][F_BK + 1];
-  __shared__ float Bs[F_BN][F_BK + 1];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r16 = lane & 15, g = lane >> 4;
-  const int d = a.d, m = a.m, n0 = nt * F_BN;
-  const int nrb = (ti.rows + 15) >> 4;
-  const float *H = static_cast<const float *>(a.act);
-  const float *wd = static_cast<const float *>(a.w0);
-  f32x4_t acc[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < m; k0 += F_BK) {
-    for (int c = tid; c < kTileM * F_BK; c += 256) {
-      const int r = c >> 4, kk = c & 15;
-      As[r][kk] = (r < ti.rows) ? H[static_cast<size_t>(ti.row0 + r) * m + k0 + kk] : 0.f;
-    }
-    {
-      const int r = tid >> 4, kk = tid & 15;
-      Bs[r][kk] = wd[(static_cast<size_t>(ti.e) * d + n0 + r) * m + k0 + kk];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < F_BK / 4; ++j) {
-      const float bv = Bs[r16][4 * j + g];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int rb = wave + 4 * i;
-        if (rb >= nrb) break;  // wave-uniform
-        acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(As[rb * 16 + r16][4 * j + g], bv, acc[i], 0, 0, 0);
-      }
-    }
-    __syncthreads();
-  }
-  float *Y = static_cast<float *>(a.out);
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int r = (wave + 4 * i) * 16 + 4 * g + q;
-      if (r < ti.rows) Y[static_cast<size_t>(ti.row0 + r) * d + n0 + r16] = acc[i][q];
-    }
 }
 
 // N tiles per workgroup.  Down: two (K is only m deep, so a tile is a short
@@ -519,43 +411,35 @@ unsigned grid_for(int max_groups, int nN) {
   return static_cast<unsigned>(8 * nN * g8);
 }
 
+template <typename T, bool GATEUP, int CG, int TPW> void launch_grouped(const GemmArgs &a, hipStream_t stream) {
+  const int nN = (GATEUP ? a.m : a.d) / tile_width<GATEUP>(CG);
+  grouped_gemm_kernel<T, GATEUP, CG, kGemmWaves, TPW>
+      <<<dim3(grid_for(a.max_groups, pairs(nN, TPW))), kGemmWaves * 64, 0, stream>>>(a);
+}
+
 }  // namespace
 
+// bf16: 128 features per gate/up tile when they divide m, else 64; 256 output columns
+// per down tile when they divide d, else 128.  fp32: 32 features, 64 columns.
 hipError_t launch_gateup(const GemmArgs &a, bool bf16, hipStream_t stream) {
   if (a.max_groups <= 0) return hipSuccess;
-  if (bf16)
-  {
-    // 128 features per tile when they divide m, else 64
-    if (a.m % tile_width<true>(8) == 0)
-      grouped_gemm_bf16_kernel<true, 8, kGemmWaves, kTpwGateUp>
-          <<<dim3(grid_for(a.max_groups, pairs(a.m / tile_width<true>(8), kTpwGateUp))), kGemmWaves * 64, 0,
-             stream>>>(a);
-    else
-      grouped_gemm_bf16_kernel<true, 4, kGemmWaves, kTpwGateUp>
-          <<<dim3(grid_for(a.max_groups, pairs(a.m / tile_width<true>(4), kTpwGateUp))), kGemmWaves * 64, 0,
-             stream>>>(a);
-  }
+  if (!bf16)
+    launch_grouped<float, true, 2, 1>(a, stream);
+  else if (a.m % tile_width<true>(8) == 0)
+    launch_grouped<bf16_t, true, 8, kTpwGateUp>(a, stream);
   else
-    gateup_f32_kernel<<<dim3(grid_for(a.max_groups, a.m / F_BN)), 256, 0, stream>>>(a);
+    launch_grouped<bf16_t, true, 4, kTpwGateUp>(a, stream);
   return hipGetLastError();
 }
 
 hipError_t launch_down(const GemmArgs &a, bool bf16, hipStream_t stream) {
   if (a.max_groups <= 0) return hipSuccess;
-  if (bf16)
-  {
-    // 256 output columns per tile when they divide d, else 128
-    if (a.d % tile_width<false>(8) == 0)
-      grouped_gemm_bf16_kernel<false, 8, kGemmWaves, kTpwDown>
-          <<<dim3(grid_for(a.max_groups, pairs(a.d / tile_width<false>(8), kTpwDown))), kGemmWaves * 64, 0,
-             stream>>>(a);
-    else
-      grouped_gemm_bf16_kernel<false, 4, kGemmWaves, kTpwDown>
-          <<<dim3(grid_for(a.max_groups, pairs(a.d / tile_width<false>(4), kTpwDown))), kGemmWaves * 64, 0,
-             stream>>>(a);
-  }
+  if (!bf16)
+    launch_grouped<float, false, 2, 1>(a, stream);
+  else if (a.d % tile_width<false>(8) == 0)
+    launch_grouped<bf16_t, false, 8, kTpwDown>(a, stream);
   else
-    down_f32_kernel<<<dim3(grid_for(a.max_groups, a.d / F_BN)), 256, 0, stream>>>(a);
+    launch_grouped<bf16_t, false, 4, kTpwDown>(a, stream);
   return hipGetLastError();
 }
 

@@ -3,7 +3,7 @@
 //
 // A tile of MB 16-row blocks (MB a multiple of 4), CG column groups (gate/up: 16
 // features each, a gate and an up block; down: 32 output columns, two blocks) and
-// KH 32-wide k halves per stage (BK = 32 KH) streams its operands through two LDS
+// KH 64-byte k halves per stage (BK = 32 KH in bf16, 16 KH in fp32) streams its operands through two LDS
 // rings: A (activation rows, mostly L2 hits) and B (expert weights, from HBM).  A
 // stage of A holds MB*KH units spread over the W waves (a wave stages na <=
 // NA_MAX of them); a stage of B holds 2*CG*KH units, NB per wave.  One unit is
@@ -27,13 +27,15 @@ template <int MB, int CG, int KH, int W> struct Pipe {
   static constexpr int NB = 2 * CG * KH / W;              // B DMAs per wave per stage
   static constexpr int ASZ = FA * kPipeUnitBytes;
   static constexpr int BSZ = 2 * CG * KH * kPipeUnitBytes;
+  // narrow tiles take half the LDS, so two workgroups share a CU
+  static constexpr int LDS = CG == 2 ? kPipeLdsBytes / 2 : kPipeLdsBytes;
   static constexpr int SA = KH == 2 ? ((MB >= 16 || (CG >= 8 && MB >= 8)) ? 2 : MB >= 8 ? 3 : 4) : 4;
-  static constexpr int SB0 = (kPipeLdsBytes - SA * ASZ) / BSZ;
+  static constexpr int SB0 = (LDS - SA * ASZ) / BSZ;
   static constexpr int SBMAX = KH == 2 ? 8 : 10;
   static constexpr int SB = SB0 > SBMAX ? SBMAX : SB0;
   static_assert(2 * CG * KH % W == 0, "B units must spread evenly over the waves");
   static_assert(SB >= 2 && SA >= 2, "ring too shallow");
-  static_assert(SA * ASZ + SB * BSZ <= kPipeLdsBytes, "rings exceed LDS");
+  static_assert(SA * ASZ + SB * BSZ <= LDS, "rings exceed LDS");
   static_assert((SA - 1) * NA_MAX + (SB - 1) * NB + NA_MAX + NB <= 63, "outstanding DMAs exceed the wait table");
 };
 
@@ -70,6 +72,21 @@ __host__ __device__ inline int pending_ok(int kt, int nk, int na) {
   }
   return cum_ops<P>(kt, nk, na) - pipe_max(end_a, end_b);
 }
+
+// pending_ok in closed form for SA <= SB: after A(kt) come the A stages kt + 1 .. kt +
+// SA - 2 and the B stages of iterations kt - SA + 1 .. kt - 1, as far as they exist (with
+// SA == SB the first of these is B(kt) itself, which is waited for too); a wave that stages no A units (na = 0) waits for B(kt)
+// alone.  Counts stay within MAX, so the wait is a choice of few constants: the
+// 64-way choice of pending_ok's count cost a narrow fp32 tile as much as its MFMAs.
+template <class P> struct Pending {
+  static_assert(P::SA <= P::SB, "the weights' ring is at least as deep");
+  static constexpr int MAX = pipe_max((P::SA - 2) * P::NA_MAX + (P::SA - 1) * P::NB, (P::SB - 2) * P::NB);
+  __host__ __device__ static int count(int kt, int nk, int na) {
+    if (na == 0) return pipe_min(P::SB - 2, nk - 1 - kt) * P::NB;
+    const int first = pipe_max(0, kt - P::SA + (P::SA == P::SB ? 2 : 1)), last = pipe_min(kt - 1, nk - P::SB);
+    return pipe_min(P::SA - 2, nk - 1 - kt) * na + pipe_max(0, last - first + 1) * P::NB;
+  }
+};
 
 // Closed form for SA == 2 < SB.  A wave that stages A units (na > 0) issues A(0)
 // last in its prologue and A(kt) as the first DMA of iteration kt - 1, followed in

@@ -1,8 +1,8 @@
-// LDS DMA helpers shared by the bf16 expert GEMMs: global -> LDS copies with
+// LDS DMA helpers shared by the expert GEMMs: global -> LDS copies with
 // global_load_lds_dwordx4 (no VGPR staging) and exact vmcnt waits.
 //
 // An "8-row unit" is what one DMA instruction moves: 8 rows x 128 bytes (a
-// 64-wide bf16 K stage of 8 rows, whole cache lines).  DMA lane i lands at
+// 64-wide bf16 or 32-wide fp32 K stage of 8 rows, whole cache lines).  DMA lane i lands at
 // byte 16*i, i.e. row i/8, slot i%8; the lane fetches chunk (i%8) ^ (i/8) of
 // its row, so chunk c of row r sits in slot c ^ r.  A 16-row block is two
 // consecutive units with the same permutation; lane l's operand of
@@ -67,6 +67,33 @@ __device__ __forceinline__ void dma16_stream(const void *src, uint32_t lds_base)
       : "memory", "m0");
 }
 
+// Operand fragments of the expert GEMMs: the 16 bytes a lane reads of its row's
+// 64-byte k half, and the products of one pair of fragments.  bf16: one
+// v_mfma_f32_16x16x32_bf16.  fp32: four v_mfma_f32_16x16x4f32, the j-th of which
+// takes element j of every lane (k = 4 g + j of the half for lane group g, in both
+// operands alike), so the layout in LDS is the same for both types.
+template <typename T> struct Frag;
+template <> struct Frag<bf16_t> {
+  typedef bf16x8_t type;
+  static constexpr int steps = 1;
+  static __device__ __forceinline__ f32x4_t mma(const type &a, const type &b, int, f32x4_t c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+  }
+};
+template <> struct Frag<float> {
+  typedef f32x4_t type;
+  static constexpr int steps = 4;
+  static __device__ __forceinline__ f32x4_t mma(const type &a, const type &b, int j, f32x4_t c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], c, 0, 0, 0);
+  }
+};
+template <typename T> constexpr int kChunkElems = 16 / static_cast<int>(sizeof(T));  // of a DMA lane
+template <typename T> constexpr int kStageElems = 128 / static_cast<int>(sizeof(T));  // k of one unit
+
+// SiLU(g) u as it is stored: see silu_for_bf16 for bf16, the exact form for fp32
+__device__ __forceinline__ bf16_t swiglu(float g, float u, bf16_t) { return f32_to_bf16(silu_for_bf16(g) * u); }
+__device__ __forceinline__ float swiglu(float g, float u, float) { return g / (1.0f + expf(-g)) * u; }
+
 __device__ __forceinline__ void barrier() { asm volatile("s_barrier" ::: "memory"); }
 
 // A 32-bit load the compiler does not track: it places no wait for it.  The
@@ -78,6 +105,19 @@ __device__ __forceinline__ int gload_i32(const int32_t *p) {
   return v;
 }
 __device__ __forceinline__ void reg_ready(int &v) { asm volatile("" : "+v"(v)::"memory"); }
+
+// wait_vmcnt for n in LO .. HI
+template <int LO, int HI> __device__ __forceinline__ void wait_vmcnt_in(int n) {
+  if constexpr (LO == HI) {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LO) : "memory");
+  } else {
+    constexpr int MID = (LO + HI) / 2;
+    if (n <= MID)
+      wait_vmcnt_in<LO, MID>(n);
+    else
+      wait_vmcnt_in<MID + 1, HI>(n);
+  }
+}
 
 // wait until at most n (0..63) of this wave's vector memory operations are outstanding
 __device__ __forceinline__ void wait_vmcnt(int n) {

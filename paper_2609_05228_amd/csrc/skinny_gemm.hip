@@ -7,10 +7,11 @@
 //    LDS ring with global_load_lds_dwordx4, one 8-row x 128-byte unit per
 //    instruction (whole cache lines; see lds_dma.h; weights carry the
 //    non-temporal hint when the wave makes one pass over them), P stages of 64 k
-//    deep, and waits only on its own vmcnt: no barriers, waves run independently;
-//  * it reads MFMA fragments back from the ring and multiplies them with
-//    v_mfma_f32_16x16x32_bf16;
-//  * with one K split the epilogue writes H (SwiGLU applied) or Y in bf16;
+//    (fp32: 32) deep, and waits only on its own vmcnt: no barriers, waves run independently;
+//  * it reads MFMA fragments back from the ring and multiplies them (Frag: bf16 or
+//    fp32; the fp32 layer of 64 tokens, 256 hidden, 8 experts of 512 took 110 us by
+//    the tiled fp32 kernels and takes 28 this way);
+//  * with one K split the epilogue writes H (SwiGLU applied) or Y in the layer's type;
 //    gate/up with several splits runs the splits of one 16-feature block as the
 //    waves of one workgroup, which add their fp32 partial sums in split order
 //    through LDS and write H (no reduction kernel); down with several splits
@@ -187,7 +188,7 @@ constexpr bool kSkinnyTwoBlocks = kSkinnyRingBytes / ((4 + 4) * kUnitBytes) >= 2
 // split): the partial sums go through red (LDS, over the workgroup's rings) and
 // wave 0 adds them in split order and writes H; every wave of the workgroup
 // calls this with the same tile rows.
-template <bool GATEUP, int MB, int AU>
+template <typename T, bool GATEUP, int MB, int AU>
 __device__ __forceinline__ void skinny_item(const SkinnyArgs &sa, const TileInfo &ti, int nb, int s, int rot,
                                             bool once, int tok, int rbase, uint8_t *ring, f32x4_t *red) {
   static_assert(AU == 2 * MB || (MB == 1 && AU == 1), "activation units cover the row blocks");
@@ -200,24 +201,26 @@ __device__ __forceinline__ void skinny_item(const SkinnyArgs &sa, const TileInfo
   const int K = GATEUP ? a.d : a.m;
   const int kc = K / sa.splits;
   const int kbase = s * kc;
-  const int nk = kc / 64;
+  constexpr int BK = kStageElems<T>;
+  typedef typename Frag<T>::type frag_t;
+  const int nk = kc / BK;
 
   // weight units t = 2 cb + j: block cb (gate/up: gate, up; down: 16-column halves), row half j
-  const bf16_t *src[NU];
+  const T *src[NU];
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
     const int cb = t >> 1, j = t & 1;
-    const int c = kbase + 8 * unit_chunk(lane);
+    const int c = kbase + kChunkElems<T> * unit_chunk(lane);
     if (GATEUP) {
       const size_t f = static_cast<size_t>(ti.e) * a.m + nb * 16 + 8 * j + ur;
-      src[t] = static_cast<const bf16_t *>(cb ? a.w1 : a.w0) + f * a.d + c;
+      src[t] = static_cast<const T *>(cb ? a.w1 : a.w0) + f * a.d + c;
     } else {
       const size_t n = static_cast<size_t>(ti.e) * a.d + nb * 32 + cb * 16 + 8 * j + ur;
-      src[t] = static_cast<const bf16_t *>(a.w0) + n * a.m + c;
+      src[t] = static_cast<const T *>(a.w0) + n * a.m + c;
     }
   }
   // activation units 4 + 2 mi + j: row block mi, row half j (AU == 1: rows 0-7 only)
-  const bf16_t *act = static_cast<const bf16_t *>(a.act);
+  const T *act = static_cast<const T *>(a.act);
 #pragma unroll
   for (int t = 4; t < NU; ++t) {
     const int mi = (t - 4) >> 1, j = t & 1;
@@ -225,7 +228,7 @@ __device__ __forceinline__ void skinny_item(const SkinnyArgs &sa, const TileInfo
     // self_plan: the token of tile row r sits in lane r of tok (tile rows <= 64;
     // this item covers tile rows rbase ..)
     const int src_row = sa.self_plan ? __shfl(tok, rbase + row) : a.perm ? a.perm[ti.row0 + row] : ti.row0 + row;
-    src[t] = act + static_cast<size_t>(src_row) * K + kbase + 8 * unit_chunk(lane);
+    src[t] = act + static_cast<size_t>(src_row) * K + kbase + kChunkElems<T> * unit_chunk(lane);
   }
   const uint32_t ring_lds = lds_addr(ring);
   // Stage st covers the 64-wide K block (st + k0) % nk of this split: waves start
@@ -239,13 +242,13 @@ __device__ __forceinline__ void skinny_item(const SkinnyArgs &sa, const TileInfo
     // weights: non-temporal when this is the item's only pass over them
     if (once) {
 #pragma unroll
-      for (int t = 0; t < 4; ++t) dma16_stream(src[t] + kb * 64, base + t * kUnitBytes);
+      for (int t = 0; t < 4; ++t) dma16_stream(src[t] + kb * BK, base + t * kUnitBytes);
     } else {
 #pragma unroll
-      for (int t = 0; t < 4; ++t) dma16(src[t] + kb * 64, base + t * kUnitBytes);
+      for (int t = 0; t < 4; ++t) dma16(src[t] + kb * BK, base + t * kUnitBytes);
     }
 #pragma unroll
-    for (int t = 4; t < NU; ++t) dma16(src[t] + kb * 64, base + t * kUnitBytes);  // activation rows
+    for (int t = 4; t < NU; ++t) dma16(src[t] + kb * BK, base + t * kUnitBytes);  // activation rows
   };
 
   f32x4_t acc[MB][2];
@@ -270,16 +273,17 @@ __device__ __forceinline__ void skinny_item(const SkinnyArgs &sa, const TileInfo
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int rd = h ? rd1 : rd0, ra = h ? ra1 : ra0;
-      bf16x8_t bf[2];
+      frag_t bf[2];
 #pragma unroll
       for (int cb = 0; cb < 2; ++cb)
-        bf[cb] = *reinterpret_cast<const bf16x8_t *>(sl + cb * 2 * kUnitBytes + rd);
+        bf[cb] = *reinterpret_cast<const frag_t *>(sl + cb * 2 * kUnitBytes + rd);
 #pragma unroll
       for (int mi = 0; mi < MB; ++mi) {
-        const bf16x8_t av = *reinterpret_cast<const bf16x8_t *>(sl + (4 + 2 * mi) * kUnitBytes + ra);
+        const frag_t av = *reinterpret_cast<const frag_t *>(sl + (4 + 2 * mi) * kUnitBytes + ra);
 #pragma unroll
-        for (int cb = 0; cb < 2; ++cb)
-          acc[mi][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bf[cb], acc[mi][cb], 0, 0, 0);
+        for (int j = 0; j < Frag<T>::steps; ++j)
+#pragma unroll
+          for (int cb = 0; cb < 2; ++cb) acc[mi][cb] = Frag<T>::mma(av, bf[cb], j, acc[mi][cb]);
       }
     }
   }
@@ -307,8 +311,7 @@ __device__ __forceinline__ void skinny_item(const SkinnyArgs &sa, const TileInfo
           }
           const int row = mi * 16 + 4 * g + q;
           if (row < ti.rows)
-            static_cast<bf16_t *>(a.out)[static_cast<size_t>(ti.row0 + row) * a.m + nb * 16 + r16] =
-                f32_to_bf16(silu_for_bf16(gs) * us);
+            static_cast<T *>(a.out)[static_cast<size_t>(ti.row0 + row) * a.m + nb * 16 + r16] = swiglu(gs, us, T{});
         }
     }
     __syncthreads();  // red is overwritten by the next pass's DMAs
@@ -323,22 +326,15 @@ __device__ __forceinline__ void skinny_item(const SkinnyArgs &sa, const TileInfo
       if (row >= ti.rows) continue;
       const size_t r = static_cast<size_t>(ti.row0 + row);
       if (GATEUP) {
-        const int f = nb * 16 + r16;
-        if (sa.splits == 1) {
-          static_cast<bf16_t *>(a.out)[r * a.m + f] = f32_to_bf16(silu_for_bf16(acc[mi][0][q]) * acc[mi][1][q]);
-        } else {
-          const size_t o = (static_cast<size_t>(s) * sa.rows_cap + r) * a.m + f;
-          sa.part0[o] = acc[mi][0][q];
-          sa.part1[o] = acc[mi][1][q];
-        }
+        static_cast<T *>(a.out)[r * a.m + nb * 16 + r16] = swiglu(acc[mi][0][q], acc[mi][1][q], T{});
       } else {
         const int n = nb * 32 + r16;
         if (sa.splits == 1) {
-          bf16_t *yr = static_cast<bf16_t *>(a.out) + r * a.d + n;
-          yr[0] = f32_to_bf16(acc[mi][0][q]);
-          yr[16] = f32_to_bf16(acc[mi][1][q]);
+          T *yr = static_cast<T *>(a.out) + r * a.d + n;
+          yr[0] = Elem<T>::from_f32(acc[mi][0][q]);
+          yr[16] = Elem<T>::from_f32(acc[mi][1][q]);
         } else {
-          float *pr = sa.part0 + (static_cast<size_t>(s) * sa.rows_cap + r) * a.d + n;
+          float *pr = sa.part + (static_cast<size_t>(s) * sa.rows_cap + r) * a.d + n;
           pr[0] = acc[mi][0][q];
           pr[16] = acc[mi][1][q];
         }
@@ -349,7 +345,7 @@ __device__ __forceinline__ void skinny_item(const SkinnyArgs &sa, const TileInfo
 // WGS = 0: one wave per work item, item = ((grp * splits) + s) * nN + nb, four
 // independent waves per workgroup.  WGS = splits (gate/up): workgroup
 // grp * nN + nb, wave s; the waves add their partial sums through LDS.
-template <bool GATEUP, int WGS>
+template <typename T, bool GATEUP, int WGS>
 __global__ __launch_bounds__((WGS ? WGS : kSkinnyWavesPerGroup) * 64) void skinny_gemm_kernel(SkinnyArgs sa) {
   constexpr int NW = WGS ? WGS : kSkinnyWavesPerGroup;
   static_assert(!WGS || GATEUP, "workgroup reduction: gate/up only");
@@ -380,14 +376,14 @@ __global__ __launch_bounds__((WGS ? WGS : kSkinnyWavesPerGroup) * 64) void skinn
   const int blocks = (ti.rows + 15) >> 4;
   const int rot = static_cast<int>(item & 0x7fffffff);
   if (ti.rows <= 8) {
-    skinny_item<GATEUP, 1, 1>(sa, ti, nb, s, rot, true, tok, 0, ring, red);
+    skinny_item<T, GATEUP, 1, 1>(sa, ti, nb, s, rot, true, tok, 0, ring, red);
   } else if (blocks <= 1 || !kSkinnyTwoBlocks) {
     // 16 rows per pass (more than 16 rows re-read the weights, mostly from L2)
     for (int r = 0; r < ti.rows; r += 16) {
       TileInfo part = ti;
       part.row0 = ti.row0 + r;
       part.rows = min(16, ti.rows - r);
-      skinny_item<GATEUP, 1, 2>(sa, part, nb, s, rot, ti.rows <= 16, tok, r, ring, red);
+      skinny_item<T, GATEUP, 1, 2>(sa, part, nb, s, rot, ti.rows <= 16, tok, r, ring, red);
     }
   } else if constexpr (kSkinnyTwoBlocks) {
     // 32 rows per pass
@@ -395,72 +391,37 @@ __global__ __launch_bounds__((WGS ? WGS : kSkinnyWavesPerGroup) * 64) void skinn
       TileInfo part = ti;
       part.row0 = ti.row0 + r;
       part.rows = min(32, ti.rows - r);
-      skinny_item<GATEUP, 2, 4>(sa, part, nb, s, rot, ti.rows <= 32, tok, r, ring, red);
+      skinny_item<T, GATEUP, 2, 4>(sa, part, nb, s, rot, ti.rows <= 32, tok, r, ring, red);
     }
   }
 }
 
-constexpr int kMaxGateUpSplits = 8;  // K splits of the small-batch gate/up GEMM
-
-// H = SiLU(sum_s gate partials) * (sum_s up partials), splits added in order.
-// All splits' partials are loaded before the first add, so the L2 round trips
-// overlap instead of following one another; the sums keep split order.
-__global__ __launch_bounds__(256) void swiglu_reduce_kernel(SkinnyArgs sa, const int32_t *n_rows) {
+template <typename T> hipError_t launch_skinny_t(const SkinnyArgs &sa, bool gateup, hipStream_t stream) {
   const GemmArgs &a = sa.g;
-  const int rows = a.dense_rows > 0 ? a.dense_rows : n_rows[0];
-  const size_t total = static_cast<size_t>(rows) * a.m;
-  bf16_t *H = static_cast<bf16_t *>(a.out);
-  const size_t plane = static_cast<size_t>(sa.rows_cap) * a.m;
-  for (size_t i = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; i < total;
-       i += static_cast<size_t>(gridDim.x) * blockDim.x) {
-    float pg[kMaxGateUpSplits], pu[kMaxGateUpSplits];
-#pragma unroll
-    for (int s = 0; s < kMaxGateUpSplits; ++s)
-      if (s < sa.splits) {
-        pg[s] = sa.part0[s * plane + i];
-        pu[s] = sa.part1[s * plane + i];
-      }
-    float gs = 0.f, us = 0.f;
-#pragma unroll
-    for (int s = 0; s < kMaxGateUpSplits; ++s) {
-      if (s >= sa.splits) break;
-      gs += pg[s];
-      us += pu[s];
-    }
-    H[i] = f32_to_bf16(silu_for_bf16(gs) * us);
-  }
-}
-
-}  // namespace
-
-hipError_t launch_skinny(const SkinnyArgs &sa, bool gateup, const int32_t *n_rows, hipStream_t stream) {
-  const GemmArgs &a = sa.g;
-  if (a.max_groups <= 0) return hipSuccess;
   const long nN = gateup ? a.m / 16 : a.d / 32;
   const long items = static_cast<long>(a.max_groups) * sa.splits * nN;
   const dim3 grid(static_cast<unsigned>((items + kSkinnyWavesPerGroup - 1) / kSkinnyWavesPerGroup));
   if (gateup) {
-    if (sa.splits > kMaxGateUpSplits) return hipErrorInvalidValue;
     // several K splits: the splits of a 16-feature block are one workgroup's waves
     const dim3 wg_grid(static_cast<unsigned>(static_cast<long>(a.max_groups) * nN));
     switch (sa.splits) {
-      case 1: skinny_gemm_kernel<true, 0><<<grid, kSkinnyWavesPerGroup * 64, 0, stream>>>(sa); break;
-      case 2: skinny_gemm_kernel<true, 2><<<wg_grid, 2 * 64, 0, stream>>>(sa); break;
-      case 4: skinny_gemm_kernel<true, 4><<<wg_grid, 4 * 64, 0, stream>>>(sa); break;
-      case 8: skinny_gemm_kernel<true, 8><<<wg_grid, 8 * 64, 0, stream>>>(sa); break;
-      default: {
-        // other split counts: partial sums, then the reduction kernel
-        skinny_gemm_kernel<true, 0><<<grid, kSkinnyWavesPerGroup * 64, 0, stream>>>(sa);
-        const size_t total = static_cast<size_t>(sa.rows_cap) * a.m;
-        size_t blocks = (total + 255) / 256;
-        if (blocks > 2048) blocks = 2048;
-        swiglu_reduce_kernel<<<dim3(static_cast<unsigned>(blocks)), 256, 0, stream>>>(sa, n_rows);
-      }
+      case 1: skinny_gemm_kernel<T, true, 0><<<grid, kSkinnyWavesPerGroup * 64, 0, stream>>>(sa); break;
+      case 2: skinny_gemm_kernel<T, true, 2><<<wg_grid, 2 * 64, 0, stream>>>(sa); break;
+      case 4: skinny_gemm_kernel<T, true, 4><<<wg_grid, 4 * 64, 0, stream>>>(sa); break;
+      case 8: skinny_gemm_kernel<T, true, 8><<<wg_grid, 8 * 64, 0, stream>>>(sa); break;
+      default: return hipErrorInvalidValue;
     }
   } else {
-    skinny_gemm_kernel<false, 0><<<grid, kSkinnyWavesPerGroup * 64, 0, stream>>>(sa);
+    skinny_gemm_kernel<T, false, 0><<<grid, kSkinnyWavesPerGroup * 64, 0, stream>>>(sa);
   }
   return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_skinny(const SkinnyArgs &sa, bool gateup, bool bf16, hipStream_t stream) {
+  if (sa.g.max_groups <= 0) return hipSuccess;
+  return bf16 ? launch_skinny_t<bf16_t>(sa, gateup, stream) : launch_skinny_t<float>(sa, gateup, stream);
 }
 
 }  // namespace ace

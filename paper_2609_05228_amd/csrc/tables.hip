@@ -21,7 +21,7 @@
 //     and W_up also gives each row's share of ||G||_F^2 and ||U||_F^2 for GSP.
 // Every reduction has a fixed order, so the tables are deterministic; fp64
 // throughout, they agree with an fp64 evaluation to ~1e-15 relative.
-#include "ace_internal.h"
+#include "lds_dma.h"
 
 namespace ace {
 
@@ -89,12 +89,14 @@ __device__ __forceinline__ double wave_sum(double v) {
 }
 
 // Sums of D o G and D o U over one 64 x 64 tile pair of one expert, 4 waves;
-// wave (wr, wc) owns a 32 x 32 sub-tile.  Bound by the fp64 matrix cores: a wave
-// issues 12 MFMAs of 64 cycles per 4 k, so its operand loads (straight from L2,
-// no LDS) only have to be covered by the other wave of its SIMD; the launch bound
-// keeps two waves per SIMD resident (one wave alone stalled at every K block:
-// 12.25 ms for 128 experts of 768 x 2048, now 9.18 ms, 51 TFLOP/s in fp64 where a
-// 4096^3 library product reaches 62).
+// wave (wr, wc) owns a 32 x 32 sub-tile.  Bound by the fp64 matrix cores (a wave
+// issues 12 MFMAs of 64 cycles per 4 k) and by the conversions to fp64, which hold
+// them up: of 8.1 ms for 128 experts of 768 x 2048 (60 TFLOP/s of the MFMAs issued; a
+// 4096^3 library product reaches 74) the conversions take 0.95 and the products with
+// gamma^2 0.3.  Operands come through two LDS stages, one copied while the other is
+// multiplied; read straight from L2 at every K block the kernel took 9.2 ms, and with
+// the next block's loads in registers they spill (15 ms).  Two waves per SIMD; three
+// measured the same.
 // gamma enters one operand of each product as gamma^2 (exact in fp64: 8 or 24 + 16
 // or 48 bits against one weight), which halves the fp64 multiplies.  Row r of a
 // sub-tile's 16-row block u is row 2 r + u, so W_down is read in adjacent column
@@ -120,42 +122,63 @@ __global__ __launch_bounds__(256, 2) void gsp_tile_kernel(TabArgs a) {
   const int d = a.d, m = a.m;
   const size_t eo = static_cast<size_t>(e) * m * d;
   const double mult = bi != bj || wr < wc ? 2.0 : wr == wc ? 1.0 : 0.0;
+  // A stage holds 4 KL k of six operands, 4 KB each: 64 rows (bi, then bj) of W_gate
+  // and of W_up, 64 bytes a row, and 64 columns (bi, bj) of W_down; then gamma's 64
+  // bytes.  Wave w copies a quarter of each.  Slot 32 s + 16 u + r of a row operand
+  // holds row 2 r + u of sub-tile s, so a fragment read is 1 KB in one piece.
+  constexpr int KB = 4 * KL, kOp = 4096, kStage = 6 * kOp + 64;
+  constexpr int kDRow = 64 * static_cast<int>(sizeof(T));  // bytes of 64 columns
+  __shared__ __align__(16) uint8_t ring[2][kStage];
+  const int srow = 32 * (wave >> 1) + 2 * (lane >> 2) + (wave & 1), schunk = KL * (lane & 3);
+  const T *wg = static_cast<const T *>(a.w_gate) + eo, *wu = static_cast<const T *>(a.w_up) + eo;
+  const size_t ra = static_cast<size_t>(bi * 64 + srow) * d + schunk, rb = static_cast<size_t>(bj * 64 + srow) * d + schunk;
+  constexpr int kPerRow = kDRow / 16;  // DMA lanes of one k of W_down
+  const T *wd = static_cast<const T *>(a.w_down) + eo +
+                static_cast<size_t>(wave * (64 / kPerRow) + lane / kPerRow) * m + KL * (lane % kPerRow);
+  const T *gam = static_cast<const T *>(a.gamma) + KL * lane;
+  auto issue = [&](int slot, int k0) {
+    const uint32_t base = lds_addr(ring[slot]) + wave * kUnitBytes;
+    dma16(wg + ra + k0, base);
+    dma16(wg + rb + k0, base + kOp);
+    dma16(wu + ra + k0, base + 2 * kOp);
+    dma16(wu + rb + k0, base + 3 * kOp);
+    dma16(wd + static_cast<size_t>(k0) * m + bi * 64, base + 4 * kOp);
+    dma16(wd + static_cast<size_t>(k0) * m + bj * 64, base + 5 * kOp);
+    if (wave == 0 && lane < 4) dma16(gam + k0, lds_addr(ring[slot]) + 6 * kOp);
+  };
   double sg = 0.0, su = 0.0;
-  if (mult != 0.0) {
-    const int ia = bi * 64 + wr * 32 + 2 * r16, jb = bj * 64 + wc * 32 + 2 * r16;
-    const T *ga_p = static_cast<const T *>(a.w_gate) + eo + static_cast<size_t>(ia) * d + KL * g;
-    const T *gb_p = static_cast<const T *>(a.w_gate) + eo + static_cast<size_t>(jb) * d + KL * g;
-    const T *ua_p = static_cast<const T *>(a.w_up) + eo + static_cast<size_t>(ia) * d + KL * g;
-    const T *ub_p = static_cast<const T *>(a.w_up) + eo + static_cast<size_t>(jb) * d + KL * g;
-    const T *da_p = static_cast<const T *>(a.w_down) + eo + static_cast<size_t>(KL * g) * m + ia;  // [d, m]
-    const T *db_p = static_cast<const T *>(a.w_down) + eo + static_cast<size_t>(KL * g) * m + jb;
-    const T *gam = static_cast<const T *>(a.gamma) + KL * g;
+  {
     f64x4_t accD[2][2], accG[2][2], accU[2][2];
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
       for (int v = 0; v < 2; ++v) accD[u][v] = accG[u][v] = accU[u][v] = f64x4_t{0.0, 0.0, 0.0, 0.0};
 
-    // blocks of 4 KL k: lane group g holds k = k0 + KL g + j and MFMA j takes element j
+    // lane group g holds k = k0 + KL g + j and MFMA j takes element j
+    const int fr = r16 * 64 + g * 16;                     // fragment offset in 16 slots
+    const int dr = KL * g * kDRow + 2 * r16 * static_cast<int>(sizeof(T));
+    issue(0, 0);
 #pragma unroll 1
-    for (int k0 = 0; k0 < d; k0 += 4 * KL) {
+    for (int k0 = 0, slot = 0; k0 < d; k0 += KB, slot ^= 1) {
+      // this stage landed for every wave, and every wave has read the other slot
+      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      if (k0 + KB < d) issue(slot ^ 1, k0 + KB);
+      if (mult == 0.0) continue;  // wave-uniform
+      const uint8_t *st = ring[slot];
       Vec<T> gm, ga[2], gb[2], ua[2], ub[2];
-      Pair<T> da[KL], db[KL];  // W_down[k][col], col = the pair of columns of this lane's two blocks
-      gm.load(gam + k0);
+      gm.load(reinterpret_cast<const T *>(st + 6 * kOp) + KL * g);
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
-        ga[u].load(ga_p + static_cast<size_t>(u) * d + k0);
-        gb[u].load(gb_p + static_cast<size_t>(u) * d + k0);
-        ua[u].load(ua_p + static_cast<size_t>(u) * d + k0);
-        ub[u].load(ub_p + static_cast<size_t>(u) * d + k0);
+        ga[u].load(reinterpret_cast<const T *>(st + (2 * wr + u) * kUnitBytes + fr));
+        gb[u].load(reinterpret_cast<const T *>(st + kOp + (2 * wc + u) * kUnitBytes + fr));
+        ua[u].load(reinterpret_cast<const T *>(st + 2 * kOp + (2 * wr + u) * kUnitBytes + fr));
+        ub[u].load(reinterpret_cast<const T *>(st + 3 * kOp + (2 * wc + u) * kUnitBytes + fr));
       }
 #pragma unroll
       for (int j = 0; j < KL; ++j) {
-        da[j].load(da_p + static_cast<size_t>(k0 + j) * m);
-        db[j].load(db_p + static_cast<size_t>(k0 + j) * m);
-      }
-#pragma unroll
-      for (int j = 0; j < KL; ++j) {
+        Pair<T> da, db;  // W_down[k][col], col = the pair of columns of this lane's two blocks
+        da.load(reinterpret_cast<const T *>(st + 4 * kOp + dr + j * kDRow + wr * (kDRow / 2)));
+        db.load(reinterpret_cast<const T *>(st + 5 * kOp + dr + j * kDRow + wc * (kDRow / 2)));
         const double gj = gm.at(j), g2 = gj * gj;
         double xa[2], xb[2];
 #pragma unroll
@@ -180,8 +203,8 @@ __global__ __launch_bounds__(256, 2) void gsp_tile_kernel(TabArgs a) {
             accU[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[u], xb[v], accU[u][v], 0, 0, 0);
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-          xa[u] = da[j].at(u);
-          xb[u] = db[j].at(u);
+          xa[u] = da.at(u);
+          xb[u] = db.at(u);
         }
 #pragma unroll
         for (int u = 0; u < 2; ++u)

@@ -132,10 +132,12 @@ struct GemmArgs {
   int dense_rows;         // > 0: dense single-group mode with this many rows
   int max_groups;         // upper bound of M tiles (grid sizing)
   int d, m;               // hidden and intermediate sizes of this GEMM's expert(s)
-  // A dense expert appended to the routed tiles (grouped GEMM): tiles
+  // A dense expert in the routed launch.  Small batches: sh_tiles = 1, its own work
+  // items ahead of the routed ones.  Grouped GEMM, appended to the routed tiles: tiles
   // n_tiles[0] .. n_tiles[0] + sh_tiles - 1 cover its rows (t - n_tiles[0]) * tile ..
   // with the identity row map, its own operands and its own output.  0: none.
   int sh_tiles, sh_rows;
+  int sh_m;               // its intermediate size (grouped GEMM: m)
   const void *sh_act, *sh_w0, *sh_w1;
   void *sh_out;
 };
@@ -147,6 +149,10 @@ struct SkinnyArgs {
   int splits;      // K splits: 1, 2, 4 or 8 (down: 1 writes Y, else partial sums)
   int rows_cap;    // row capacity of a partial-sum plane (T * k)
   float *part;     // down with several splits: Y partials [splits, rows_cap, d]
+  // the dense expert (g.sh_tiles): K splits of its down GEMM, and their partial sums
+  // [sh_splits, sh_rows, d] (1: it writes g.sh_out)
+  int sh_splits;
+  float *sh_part;
   // self_plan (routed gate/up, 2-4 router chunks): each wave derives its tile (the
   // grp-th expert with kept slots) and the tokens of its rows from the router's
   // per-chunk counts and the routing, instead of reading a plan; one item per
@@ -167,6 +173,8 @@ struct CombineArgs {
   const float *Ypart;     // [ysplits, rows_cap, d] fp32 partial sums of Y, or null
   int ysplits, rows_cap;
   const void *Ys;         // [T, d] shared-expert output, or null
+  const float *Yspart;    // [sh_splits, T, d] fp32 partial sums of it, or null
+  int sh_splits;
   const int32_t *slot_row;  // [T, k]
   const float *gates;       // [T, k]
   void *y;                // [T, d]

@@ -39,14 +39,14 @@ int pick_splits(long items, int K) {
 
 struct Layout {
   size_t xn, zpart, sspart, local_rank, chunk_count, chunk_base, slot_row, gates, counts, offsets, perm;
-  size_t tile_e, tile_r0, tile_rows, tile_ord, n_tiles, H, Y, Hs, Ys, part_y, total;
+  size_t tile_e, tile_r0, tile_rows, tile_ord, n_tiles, H, Y, Hs, Ys, part_y, part_ys, total;
   int G, tile_m, max_groups, dense_groups;
   bool skinny;          // small-batch path (T <= kSkinnyMaxT)
-  int splits_gu, splits_dn;
+  int splits_gu, splits_dn, splits_sh;
   int ksplit, zstride;  // router K slices (0: fused) and partial-logit row stride
 };
 
-Layout layout_of(const ace_moe_desc &d, bool split_down) {
+Layout layout_of(const ace_moe_desc &d, bool split_down, bool split_shared) {
   Layout L{};
   const size_t T = static_cast<size_t>(d.T), dd = static_cast<size_t>(d.d);
   const size_t N = static_cast<size_t>(d.N), k = static_cast<size_t>(d.k), m = static_cast<size_t>(d.m);
@@ -62,11 +62,12 @@ Layout layout_of(const ace_moe_desc &d, bool split_down) {
   }
   L.zstride = 16 * ace::route_expert_tiles(d.N);
   L.skinny = d.T <= kSkinnyMaxT;
-  L.splits_gu = L.splits_dn = 1;
+  L.splits_gu = L.splits_dn = L.splits_sh = 1;
   if (L.skinny) {
     const long tiles = static_cast<long>(slots < N ? slots : N);
     L.splits_gu = pick_splits(tiles * (d.m / 16), d.d);
     if (split_down) L.splits_dn = pick_splits(tiles * (d.d / 32), d.m);
+    if (split_shared && d.n_shared > 0) L.splits_sh = pick_splits(d.d / 32, d.m_shared);
   }
   L.tile_m = d.dtype == ACE_F32 && !L.skinny ? ace::kTileMF32 : ace::kTileM;
   L.max_groups = static_cast<int>((slots + L.tile_m - 1) / L.tile_m + (slots < N ? slots : N));
@@ -99,16 +100,18 @@ Layout layout_of(const ace_moe_desc &d, bool split_down) {
     L.Hs = take(T * static_cast<size_t>(d.m_shared) * esz);
     L.Ys = take(T * dd * esz);
   }
+  if (L.splits_sh > 1) L.part_ys = take(static_cast<size_t>(L.splits_sh) * T * dd * 4);
   if (L.splits_dn > 1) L.part_y = take(static_cast<size_t>(L.splits_dn) * slots * dd * 4);
   L.total = off;
   return L;
 }
 
-// An fp32 layer whose partial sums of the K-split down GEMM would not fit the static
-// scratch goes without the split, so that what fits it without them still does.
+// A layer that the partial sums of the shared expert's K-split down GEMM, or in fp32 of
+// the routed one, take beyond the static scratch goes without these splits, so that what
+// fits it without them still does.
 Layout layout_for(const ace_moe_desc &d) {
-  const Layout L = layout_of(d, true);
-  return d.dtype == ACE_F32 && L.splits_dn > 1 && L.total > ACE_NOALLOC_SCRATCH_BYTES ? layout_of(d, false) : L;
+  const Layout L = layout_of(d, true, true);
+  return L.total > ACE_NOALLOC_SCRATCH_BYTES ? layout_of(d, d.dtype == ACE_BF16, false) : L;
 }
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -527,15 +530,18 @@ ace_status forward_impl(const ace_moe_desc *desc, const void *x, const ace_moe_w
   gd.w0 = w->w_down;
   gd.w1 = nullptr;
   gd.out = at(L.Y);
-  // a shared expert with the routed experts' intermediate size runs as extra M tiles
-  // of the routed grouped GEMMs (one launch each instead of two half-filled ones)
-  const bool shared_in_routed = d.n_shared == 1 && !L.skinny && d.m_shared == d.m;
+  // a shared expert runs in the routed launches of a small batch (as work items of its
+  // own) and, with the routed experts' intermediate size, of the grouped GEMMs (as extra
+  // M tiles): one launch each instead of two half-filled ones
+  const bool shared_in_routed = d.n_shared == 1 && (L.skinny || d.m_shared == d.m);
   if (shared_in_routed) {
-    const int st = L.dense_groups;
+    const int st = L.skinny ? 1 : L.dense_groups;
     g.sh_tiles = gd.sh_tiles = st;
     g.sh_rows = gd.sh_rows = d.T;
-    g.max_groups += st;
-    gd.max_groups += st;
+    if (!L.skinny) {
+      g.max_groups += st;
+      gd.max_groups += st;
+    }
     g.sh_act = at(L.xn);
     g.sh_w0 = w->ws_gate;
     g.sh_w1 = w->ws_up;
@@ -544,6 +550,7 @@ ace_status forward_impl(const ace_moe_desc *desc, const void *x, const ace_moe_w
     gd.sh_w0 = w->ws_down;
     gd.sh_w1 = nullptr;
     gd.sh_out = at(L.Ys);
+    g.sh_m = gd.sh_m = d.m_shared;
   }
   if (L.skinny) {
     const int slots = d.T * d.k;
@@ -568,7 +575,8 @@ ace_status forward_impl(const ace_moe_desc *desc, const void *x, const ace_moe_w
     }
     if (ace::launch_skinny(su, true, bf16, stream) != hipSuccess) return ACE_ERR_HIP;
     mark(prof, 3, stream);
-    ace::SkinnyArgs sd{gd, L.splits_dn, slots, static_cast<float *>(at(L.part_y))};
+    ace::SkinnyArgs sd{gd, L.splits_dn, slots, static_cast<float *>(at(L.part_y)), L.splits_sh,
+                       static_cast<float *>(at(L.part_ys))};
     if (ace::launch_skinny(sd, false, bf16, stream) != hipSuccess) return ACE_ERR_HIP;
   } else {
     if (ace::launch_gateup(g, bf16, stream) != hipSuccess) return ACE_ERR_HIP;
@@ -594,15 +602,8 @@ ace_status forward_impl(const ace_moe_desc *desc, const void *x, const ace_moe_w
     sd.w0 = w->ws_down;
     sd.w1 = nullptr;
     sd.out = at(L.Ys);
-    if (L.skinny) {
-      ace::SkinnyArgs su{s, 1, d.T, nullptr};
-      ace::SkinnyArgs sdn{sd, 1, d.T, nullptr};
-      if (ace::launch_skinny(su, true, bf16, stream) != hipSuccess) return ACE_ERR_HIP;
-      if (ace::launch_skinny(sdn, false, bf16, stream) != hipSuccess) return ACE_ERR_HIP;
-    } else {
-      if (ace::launch_gateup(s, bf16, stream) != hipSuccess) return ACE_ERR_HIP;
-      if (ace::launch_down(sd, bf16, stream) != hipSuccess) return ACE_ERR_HIP;
-    }
+    if (ace::launch_gateup(s, bf16, stream) != hipSuccess) return ACE_ERR_HIP;
+    if (ace::launch_down(sd, bf16, stream) != hipSuccess) return ACE_ERR_HIP;
     Ys = at(L.Ys);
   }
   mark(prof, 5, stream, d.n_shared == 1 && !shared_in_routed);
@@ -612,7 +613,10 @@ ace_status forward_impl(const ace_moe_desc *desc, const void *x, const ace_moe_w
   c.Ypart = L.splits_dn > 1 ? static_cast<const float *>(at(L.part_y)) : nullptr;
   c.ysplits = L.splits_dn;
   c.rows_cap = d.T * d.k;
-  c.Ys = Ys;
+  const bool shared_split = d.n_shared == 1 && L.splits_sh > 1;
+  c.Ys = shared_split ? nullptr : Ys;
+  c.Yspart = shared_split ? static_cast<const float *>(at(L.part_ys)) : nullptr;
+  c.sh_splits = L.splits_sh;
   c.slot_row = slot_row;
   c.gates = gates;
   c.y = out->y;

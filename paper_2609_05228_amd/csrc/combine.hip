@@ -9,12 +9,15 @@
 //  * K-split partials (small batches): one workgroup per (128-column block,
 //    token); thread (slot i, 4 columns) sums slot i's partials in split order
 //    with every load in flight at once, then one thread per 4 columns adds the
-//    slots in slot order.
+//    slots in slot order;
+//  * the shared expert's partials (small batches) likewise, in split order.
 #include "ace_internal.h"
 
 namespace ace {
 
 namespace {
+
+constexpr int kMaxSplits = 8;  // K splits of the small-batch down GEMMs
 
 template <typename T> struct V;
 template <> struct V<bf16_t> {
@@ -80,6 +83,29 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
       if (rows[i] >= 0) q[i] = V<T>::load(Y + static_cast<size_t>(rows[i]) * a.d + c);
     typename V<T>::raw qs;
     if (Ys) qs = V<T>::load(Ys + static_cast<size_t>(t) * a.d + c);
+    float sh[VN];
+    if (a.Yspart) {
+      // the shared expert's partial sums, every load in flight before the first add
+      float4 p[kMaxSplits][VN / 4];
+#pragma unroll
+      for (int s = 0; s < kMaxSplits; ++s)
+        if (s < a.sh_splits)
+#pragma unroll
+          for (int j = 0; j < VN / 4; ++j)
+            p[s][j] = *reinterpret_cast<const float4 *>(a.Yspart + (static_cast<size_t>(s) * a.T + t) * a.d + c + 4 * j);
+#pragma unroll
+      for (int j = 0; j < VN; ++j) sh[j] = 0.f;
+#pragma unroll
+      for (int s = 0; s < kMaxSplits; ++s)
+        if (s < a.sh_splits)
+#pragma unroll
+          for (int j = 0; j < VN / 4; ++j) {
+            sh[4 * j] += p[s][j].x;
+            sh[4 * j + 1] += p[s][j].y;
+            sh[4 * j + 2] += p[s][j].z;
+            sh[4 * j + 3] += p[s][j].w;
+          }
+    }
     float acc[VN];
 #pragma unroll
     for (int j = 0; j < VN; ++j) acc[j] = 0.f;
@@ -98,16 +124,20 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
 #pragma unroll
       for (int j = 0; j < VN; ++j) acc[j] += v[j];
     }
+    if (a.Yspart) {
+#pragma unroll
+      for (int j = 0; j < VN; ++j) acc[j] += sh[j];
+    }
     V<T>::store(y + static_cast<size_t>(t) * a.d + c, acc);
   }
 }
 
 constexpr int kSplitCols = 128;  // columns of one split-combine workgroup
-constexpr int kMaxSplits = 8;    // K splits of the small-batch down GEMM
 
 template <typename T>
 __global__ __launch_bounds__(256) void combine_split_kernel(CombineArgs a) {
   __shared__ float vs[kMaxK][kSplitCols + 4];
+  __shared__ float4 sh[kMaxSplits][kSplitCols / 4];  // the shared expert's partial sums
   __shared__ int rows[kMaxK];
   __shared__ float gs[kMaxK];
   const int t = blockIdx.y;
@@ -120,6 +150,9 @@ __global__ __launch_bounds__(256) void combine_split_kernel(CombineArgs a) {
   __syncthreads();
   const int i = tid >> 5, cg = tid & 31;  // slot, 4-column group
   const int c = blockIdx.x * kSplitCols + 4 * cg;
+  static_assert(256 / 32 == kMaxSplits && kMaxSplits == kMaxK, "a thread row per slot and per split");
+  if (a.Yspart && i < a.sh_splits)
+    sh[i][cg] = *reinterpret_cast<const float4 *>(a.Yspart + (static_cast<size_t>(i) * a.T + t) * a.d + c);
   const int r = rows[i];
   if (r >= 0) {
     float4 q[kMaxSplits];
@@ -151,6 +184,18 @@ __global__ __launch_bounds__(256) void combine_split_kernel(CombineArgs a) {
     if (a.Ys) {
       float v[4];
       V<T>::load4(static_cast<const T *>(a.Ys) + static_cast<size_t>(t) * a.d + c, v);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[j] += v[j];
+    }
+    if (a.Yspart) {
+      float v[4] = {0.f, 0.f, 0.f, 0.f};
+      for (int s = 0; s < a.sh_splits; ++s) {
+        const float4 p = sh[s][tid];
+        v[0] += p.x;
+        v[1] += p.y;
+        v[2] += p.z;
+        v[3] += p.w;
+      }
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[j] += v[j];
     }

@@ -153,17 +153,10 @@ __device__ TileInfo self_tile(const SkinnyArgs &sa, int grp, bool write_slots, b
 
 __device__ __forceinline__ TileInfo skinny_tile(const GemmArgs &a, int grp) {
   TileInfo ti;
-  if (a.dense_rows > 0) {
-    ti.e = 0;
-    ti.row0 = grp * kTileM;
-    ti.rows = min(kTileM, a.dense_rows - ti.row0);
-    ti.valid = ti.rows > 0;
-  } else {
-    ti.valid = grp < a.n_tiles[0];
-    ti.e = ti.valid ? a.tile_expert[grp] : 0;
-    ti.row0 = ti.valid ? a.tile_row0[grp] : 0;
-    ti.rows = ti.valid ? a.tile_rows[grp] : 0;
-  }
+  ti.valid = grp < a.n_tiles[0];
+  ti.e = ti.valid ? a.tile_expert[grp] : 0;
+  ti.row0 = ti.valid ? a.tile_row0[grp] : 0;
+  ti.rows = ti.valid ? a.tile_rows[grp] : 0;
   return ti;
 }
 
@@ -184,22 +177,31 @@ template <int AU> struct SkinnyRing {
 // whether a ring holds two stages of a 32-row (two-block) item
 constexpr bool kSkinnyTwoBlocks = kSkinnyRingBytes / ((4 + 4) * kUnitBytes) >= 2;
 
+// Operands of one work item: the routed experts' or the dense expert's
+struct Op {
+  const void *act, *w0, *w1;
+  void *out;
+  const int32_t *perm;
+  float *part;
+  int m, splits, rows_cap;
+  bool self_plan;
+};
+
 // red != null (gate/up, K splits as the waves of one workgroup, wave index =
 // split): the partial sums go through red (LDS, over the workgroup's rings) and
 // wave 0 adds them in split order and writes H; every wave of the workgroup
 // calls this with the same tile rows.
 template <typename T, bool GATEUP, int MB, int AU>
-__device__ __forceinline__ void skinny_item(const SkinnyArgs &sa, const TileInfo &ti, int nb, int s, int rot,
+__device__ __forceinline__ void skinny_item(const Op &op, int d, const TileInfo &ti, int nb, int s, int rot,
                                             bool once, int tok, int rbase, uint8_t *ring, f32x4_t *red) {
   static_assert(AU == 2 * MB || (MB == 1 && AU == 1), "activation units cover the row blocks");
   using R = SkinnyRing<AU>;
   constexpr int P = R::P, NU = R::NU;
-  const GemmArgs &a = sa.g;
   const int lane = threadIdx.x & 63;
   const int r16 = lane & 15, g = lane >> 4;
   const int ur = lane >> 3;  // DMA lane -> row in its unit
-  const int K = GATEUP ? a.d : a.m;
-  const int kc = K / sa.splits;
+  const int K = GATEUP ? d : op.m;
+  const int kc = K / op.splits;
   const int kbase = s * kc;
   constexpr int BK = kStageElems<T>;
   typedef typename Frag<T>::type frag_t;
@@ -212,22 +214,22 @@ __device__ __forceinline__ void skinny_item(const SkinnyArgs &sa, const TileInfo
     const int cb = t >> 1, j = t & 1;
     const int c = kbase + kChunkElems<T> * unit_chunk(lane);
     if (GATEUP) {
-      const size_t f = static_cast<size_t>(ti.e) * a.m + nb * 16 + 8 * j + ur;
-      src[t] = static_cast<const T *>(cb ? a.w1 : a.w0) + f * a.d + c;
+      const size_t f = static_cast<size_t>(ti.e) * op.m + nb * 16 + 8 * j + ur;
+      src[t] = static_cast<const T *>(cb ? op.w1 : op.w0) + f * d + c;
     } else {
-      const size_t n = static_cast<size_t>(ti.e) * a.d + nb * 32 + cb * 16 + 8 * j + ur;
-      src[t] = static_cast<const T *>(a.w0) + n * a.m + c;
+      const size_t n = static_cast<size_t>(ti.e) * d + nb * 32 + cb * 16 + 8 * j + ur;
+      src[t] = static_cast<const T *>(op.w0) + n * op.m + c;
     }
   }
   // activation units 4 + 2 mi + j: row block mi, row half j (AU == 1: rows 0-7 only)
-  const T *act = static_cast<const T *>(a.act);
+  const T *act = static_cast<const T *>(op.act);
 #pragma unroll
   for (int t = 4; t < NU; ++t) {
     const int mi = (t - 4) >> 1, j = t & 1;
     const int row = min(mi * 16 + 8 * j + ur, ti.rows - 1);  // rows past the tile repeat its last row
     // self_plan: the token of tile row r sits in lane r of tok (tile rows <= 64;
     // this item covers tile rows rbase ..)
-    const int src_row = sa.self_plan ? __shfl(tok, rbase + row) : a.perm ? a.perm[ti.row0 + row] : ti.row0 + row;
+    const int src_row = op.self_plan ? __shfl(tok, rbase + row) : op.perm ? op.perm[ti.row0 + row] : ti.row0 + row;
     src[t] = act + static_cast<size_t>(src_row) * K + kbase + kChunkElems<T> * unit_chunk(lane);
   }
   const uint32_t ring_lds = lds_addr(ring);
@@ -305,13 +307,13 @@ __device__ __forceinline__ void skinny_item(const SkinnyArgs &sa, const TileInfo
         for (int q = 0; q < 4; ++q) {
           // the splits in order from zero, as a separate reduction would add them
           float gs = 0.f, us = 0.f;
-          for (int sp = 0; sp < sa.splits; ++sp) {
+          for (int sp = 0; sp < op.splits; ++sp) {
             gs += red[((sp * MB + mi) * 2 + 0) * 64 + lane][q];
             us += red[((sp * MB + mi) * 2 + 1) * 64 + lane][q];
           }
           const int row = mi * 16 + 4 * g + q;
           if (row < ti.rows)
-            static_cast<T *>(a.out)[static_cast<size_t>(ti.row0 + row) * a.m + nb * 16 + r16] = swiglu(gs, us, T{});
+            static_cast<T *>(op.out)[static_cast<size_t>(ti.row0 + row) * op.m + nb * 16 + r16] = swiglu(gs, us, T{});
         }
     }
     __syncthreads();  // red is overwritten by the next pass's DMAs
@@ -326,15 +328,15 @@ __device__ __forceinline__ void skinny_item(const SkinnyArgs &sa, const TileInfo
       if (row >= ti.rows) continue;
       const size_t r = static_cast<size_t>(ti.row0 + row);
       if (GATEUP) {
-        static_cast<T *>(a.out)[r * a.m + nb * 16 + r16] = swiglu(acc[mi][0][q], acc[mi][1][q], T{});
+        static_cast<T *>(op.out)[r * op.m + nb * 16 + r16] = swiglu(acc[mi][0][q], acc[mi][1][q], T{});
       } else {
         const int n = nb * 32 + r16;
-        if (sa.splits == 1) {
-          T *yr = static_cast<T *>(a.out) + r * a.d + n;
+        if (op.splits == 1) {
+          T *yr = static_cast<T *>(op.out) + r * d + n;
           yr[0] = Elem<T>::from_f32(acc[mi][0][q]);
           yr[16] = Elem<T>::from_f32(acc[mi][1][q]);
         } else {
-          float *pr = sa.part + (static_cast<size_t>(s) * sa.rows_cap + r) * a.d + n;
+          float *pr = op.part + (static_cast<size_t>(s) * op.rows_cap + r) * d + n;
           pr[0] = acc[mi][0][q];
           pr[16] = acc[mi][1][q];
         }
@@ -342,9 +344,19 @@ __device__ __forceinline__ void skinny_item(const SkinnyArgs &sa, const TileInfo
     }
 }
 
+// work items of the dense expert in a launch (WGS > 0: workgroups)
+__host__ __device__ inline int shared_items(const SkinnyArgs &sa, bool gateup) {
+  if (!sa.g.sh_tiles) return 0;
+  return gateup ? sa.g.sh_m / 16 : sa.sh_splits * (sa.g.d / 32);
+}
+
 // WGS = 0: one wave per work item, item = ((grp * splits) + s) * nN + nb, four
 // independent waves per workgroup.  WGS = splits (gate/up): workgroup
-// grp * nN + nb, wave s; the waves add their partial sums through LDS.
+// grp * nN + nb, wave s; the waves add their partial sums through LDS.  The dense
+// expert's items come first (it has every token's row): as two unsplit launches of
+// their own they took 8-29 us of a small batch (3 tokens, 1792 hidden, 38 experts of
+// 128 and a shared one: 35.7 us a layer, now 23.7; 33 tokens, 2048 hidden, a shared
+// expert of 1024: 81.2, now 52.0).
 template <typename T, bool GATEUP, int WGS>
 __global__ __launch_bounds__((WGS ? WGS : kSkinnyWavesPerGroup) * 64) void skinny_gemm_kernel(SkinnyArgs sa) {
   constexpr int NW = WGS ? WGS : kSkinnyWavesPerGroup;
@@ -353,37 +365,52 @@ __global__ __launch_bounds__((WGS ? WGS : kSkinnyWavesPerGroup) * 64) void skinn
   __shared__ __align__(16) uint8_t smem[NW * kSkinnyRingBytes];
   const GemmArgs &a = sa.g;
   const int nN = GATEUP ? a.m / 16 : a.d / 32;
-  const int wave = threadIdx.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint8_t *ring = smem + wave * kSkinnyRingBytes;
   f32x4_t *red = WGS ? reinterpret_cast<f32x4_t *>(smem) : nullptr;
-  const long item = static_cast<long>(blockIdx.x) * NW + wave;
-  int nb, s, grp;
+  const int nS = shared_items(sa, GATEUP);
+  const long first = static_cast<long>(nS) * (WGS ? NW : 1);  // first routed item
+  const long item = static_cast<long>(blockIdx.x) * NW + wave - first;
+  const bool shared = item < 0;
+  int nb, s, grp = 0;
   if constexpr (WGS > 0) {
-    nb = static_cast<int>(blockIdx.x % nN);
-    grp = static_cast<int>(blockIdx.x / nN);
+    const int b = static_cast<int>(blockIdx.x) - nS;
+    nb = shared ? static_cast<int>(blockIdx.x) : b % nN;
+    grp = shared ? 0 : b / nN;
     s = wave;
   } else {
-    nb = static_cast<int>(item % nN);
-    const long rest = item / nN;
-    s = static_cast<int>(rest % sa.splits);
-    grp = static_cast<int>(rest / sa.splits);
+    const long i = shared ? item + first : item;
+    // the dense expert: gate/up, nS feature blocks of one split; down, its splits of nN blocks
+    const int n = shared && GATEUP ? nS : nN;
+    nb = static_cast<int>(i % n);
+    const long rest = i / n;
+    s = shared ? static_cast<int>(rest) : static_cast<int>(rest % sa.splits);
+    grp = shared ? 0 : static_cast<int>(rest / sa.splits);
   }
-  if (grp >= a.max_groups) return;
+  if (!shared && grp >= a.max_groups) return;
   int tok = 0;
-  const TileInfo ti = (GATEUP && sa.self_plan) ? self_tile(sa, grp, nb == 0 && s == 0, item == 0, &tok)
-                                              : skinny_tile(a, grp);
+  TileInfo ti;
+  Op op;
+  if (shared) {
+    ti = TileInfo{0, 0, a.sh_rows, true};
+    op = Op{a.sh_act, a.sh_w0, a.sh_w1, a.sh_out, nullptr, sa.sh_part, a.sh_m, GATEUP ? sa.splits : sa.sh_splits,
+            a.sh_rows, false};
+  } else {
+    ti = (GATEUP && sa.self_plan) ? self_tile(sa, grp, nb == 0 && s == 0, item == 0, &tok) : skinny_tile(a, grp);
+    op = Op{a.act, a.w0, a.w1, a.out, a.perm, sa.part, a.m, sa.splits, sa.rows_cap, sa.self_plan};
+  }
   if (!ti.valid) return;
   const int blocks = (ti.rows + 15) >> 4;
-  const int rot = static_cast<int>(item & 0x7fffffff);
+  const int rot = static_cast<int>((item + first) & 0x7fffffff);
   if (ti.rows <= 8) {
-    skinny_item<T, GATEUP, 1, 1>(sa, ti, nb, s, rot, true, tok, 0, ring, red);
+    skinny_item<T, GATEUP, 1, 1>(op, a.d, ti, nb, s, rot, true, tok, 0, ring, red);
   } else if (blocks <= 1 || !kSkinnyTwoBlocks) {
     // 16 rows per pass (more than 16 rows re-read the weights, mostly from L2)
     for (int r = 0; r < ti.rows; r += 16) {
       TileInfo part = ti;
       part.row0 = ti.row0 + r;
       part.rows = min(16, ti.rows - r);
-      skinny_item<T, GATEUP, 1, 2>(sa, part, nb, s, rot, ti.rows <= 16, tok, r, ring, red);
+      skinny_item<T, GATEUP, 1, 2>(op, a.d, part, nb, s, rot, ti.rows <= 16, tok, r, ring, red);
     }
   } else if constexpr (kSkinnyTwoBlocks) {
     // 32 rows per pass
@@ -391,7 +418,7 @@ __global__ __launch_bounds__((WGS ? WGS : kSkinnyWavesPerGroup) * 64) void skinn
       TileInfo part = ti;
       part.row0 = ti.row0 + r;
       part.rows = min(32, ti.rows - r);
-      skinny_item<T, GATEUP, 2, 4>(sa, part, nb, s, rot, ti.rows <= 32, tok, r, ring, red);
+      skinny_item<T, GATEUP, 2, 4>(op, a.d, part, nb, s, rot, ti.rows <= 32, tok, r, ring, red);
     }
   }
 }
@@ -399,11 +426,11 @@ __global__ __launch_bounds__((WGS ? WGS : kSkinnyWavesPerGroup) * 64) void skinn
 template <typename T> hipError_t launch_skinny_t(const SkinnyArgs &sa, bool gateup, hipStream_t stream) {
   const GemmArgs &a = sa.g;
   const long nN = gateup ? a.m / 16 : a.d / 32;
-  const long items = static_cast<long>(a.max_groups) * sa.splits * nN;
+  const long items = static_cast<long>(a.max_groups) * sa.splits * nN + shared_items(sa, gateup);
   const dim3 grid(static_cast<unsigned>((items + kSkinnyWavesPerGroup - 1) / kSkinnyWavesPerGroup));
   if (gateup) {
     // several K splits: the splits of a 16-feature block are one workgroup's waves
-    const dim3 wg_grid(static_cast<unsigned>(static_cast<long>(a.max_groups) * nN));
+    const dim3 wg_grid(static_cast<unsigned>(static_cast<long>(a.max_groups) * nN + shared_items(sa, gateup)));
     switch (sa.splits) {
       case 1: skinny_gemm_kernel<T, true, 0><<<grid, kSkinnyWavesPerGroup * 64, 0, stream>>>(sa); break;
       case 2: skinny_gemm_kernel<T, true, 2><<<wg_grid, 2 * 64, 0, stream>>>(sa); break;

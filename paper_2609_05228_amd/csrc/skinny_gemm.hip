@@ -153,10 +153,12 @@ __device__ TileInfo self_tile(const SkinnyArgs &sa, int grp, bool write_slots, b
 
 __device__ __forceinline__ TileInfo skinny_tile(const GemmArgs &a, int grp) {
   TileInfo ti;
-  ti.valid = grp < a.n_tiles[0];
-  ti.e = ti.valid ? a.tile_expert[grp] : 0;
-  ti.row0 = ti.valid ? a.tile_row0[grp] : 0;
-  ti.rows = ti.valid ? a.tile_rows[grp] : 0;
+  // the loads go out together (grp < max_groups, the lists' size)
+  const int nr = a.n_tiles[0], e = a.tile_expert[grp], row0 = a.tile_row0[grp], rows = a.tile_rows[grp];
+  ti.valid = grp < nr;
+  ti.e = ti.valid ? e : 0;
+  ti.row0 = ti.valid ? row0 : 0;
+  ti.rows = ti.valid ? rows : 0;
   return ti;
 }
 

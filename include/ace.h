@@ -176,8 +176,7 @@ ace_status ace_moe_forward_noalloc(const ace_moe_desc *desc, const void *x, cons
  *   1 plan   (expert histogram and prefix sums, permutation, M tiles)
  *   2 gateup (grouped gate/up GEMM with the SwiGLU epilogue)
  *   3 down   (grouped down GEMM)
- *   4 shared (dense shared expert; empty when n_shared = 0 or its GEMMs run in the
- *     launches of stages 2 and 3)
+ *   4 shared (always empty: the shared expert's GEMMs run in stages 2 and 3)
  *   5 combine.
  * ace_profile_end waits for the recorded events, writes the per-stage elapsed
  * time summed over the recorded calls (ms) into stage_ms[0..n_stages-1] and the

@@ -137,7 +137,8 @@ struct GemmArgs {
   // n_tiles[0] .. n_tiles[0] + sh_tiles - 1 cover its rows (t - n_tiles[0]) * tile ..
   // with the identity row map, its own operands and its own output.  0: none.
   int sh_tiles, sh_rows;
-  int sh_m;               // its intermediate size (grouped GEMM: m)
+  int sh_m;               // its intermediate size
+  int sh_block0;          // gate/up, sh_m != m: first block of its tiles' own part of the grid (sh_tiles = 0), else 0
   const void *sh_act, *sh_w0, *sh_w1;
   void *sh_out;
 };
@@ -186,6 +187,8 @@ struct CombineArgs {
 hipError_t launch_route(const RouteArgs &a, bool bf16, hipStream_t stream);
 hipError_t launch_plan(const PlanArgs &a, hipStream_t stream);
 hipError_t launch_gateup(const GemmArgs &a, bool bf16, hipStream_t stream);
+// whether the routed gate/up launch's tiles (by the routed size m) divide a dense expert of size sh_m
+bool gateup_takes_dense(int m, int sh_m, bool bf16);
 hipError_t launch_down(const GemmArgs &a, bool bf16, hipStream_t stream);
 hipError_t launch_combine(const CombineArgs &a, bool bf16, hipStream_t stream);
 // whether launch_plan writes PlanArgs::tile_order for these sizes (the one-kernel plan)

@@ -114,7 +114,7 @@ template <int CG> constexpr int stage_halves() { return 2; }
 
 // Output stores of gemm_tile: lane holds column r16 of each block, rows 4*g + q.
 template <typename T, bool GATEUP, int MW, int CW, int RW, int BN>
-__device__ __forceinline__ void store_tile_impl(const GemmArgs &a, const TileInfo &ti, void *outp,
+__device__ __forceinline__ void store_tile_impl(int ld, const TileInfo &ti, void *outp,
                                                 f32x4_t (&acc)[MW][2 * CW], int nt, int wr, int wc, int r16, int g) {
 #pragma unroll
   for (int fl = 0; fl < CW; ++fl) {
@@ -128,7 +128,7 @@ __device__ __forceinline__ void store_tile_impl(const GemmArgs &a, const TileInf
         for (int q = 0; q < 4; ++q) {
           const int row = (wr + RW * i) * 16 + 4 * g + q;
           if (row < ti.rows)
-            H[static_cast<size_t>(ti.row0 + row) * a.m + f] = swiglu(acc[i][fl * 2][q], acc[i][fl * 2 + 1][q], T{});
+            H[static_cast<size_t>(ti.row0 + row) * ld + f] = swiglu(acc[i][fl * 2][q], acc[i][fl * 2 + 1][q], T{});
         }
     } else {
       T *Y = static_cast<T *>(outp);
@@ -139,7 +139,7 @@ __device__ __forceinline__ void store_tile_impl(const GemmArgs &a, const TileInf
         for (int q = 0; q < 4; ++q) {
           const int row = (wr + RW * i) * 16 + 4 * g + q;
           if (row < ti.rows) {
-            T *yr = Y + static_cast<size_t>(ti.row0 + row) * a.d + n;
+            T *yr = Y + static_cast<size_t>(ti.row0 + row) * ld + n;
             yr[0] = Elem<T>::from_f32(acc[i][fl * 2][q]);
             yr[16] = Elem<T>::from_f32(acc[i][fl * 2 + 1][q]);
           }
@@ -161,7 +161,7 @@ __device__ __forceinline__ void store_tile_impl(const GemmArgs &a, const TileInf
 // c ^ r (both units of a block alike), so the MFMA fragment reads (16 rows, one
 // chunk each) run at the full LDS rate.  Wave w computes row blocks wr, wr+RW,
 // ... (wr = w/2) against the CG/2 column groups starting at wc*CG/2 (wc = w%2).
-template <typename T, bool GATEUP, int MB, int CG, int KH, int W>
+template <typename T, bool GATEUP, int MB, int CG, int KH, int W, bool OWN>
 __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const TileInfo &ti, int nt0, int ntiles, int erot,
                                           uint8_t *smem) {
   static_assert(KH == 2, "8-row DMA units span a 64-wide K stage");
@@ -177,7 +177,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const TileInfo &ti,
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r16 = lane & 15, g = lane >> 4;
   const int wr = wave >> 1, wc = wave & 1;
-  const int K = GATEUP ? a.d : a.m;
+  const int m = OWN && ti.sh ? a.sh_m : a.m;
+  const int K = GATEUP ? a.d : m;
   // routed tile: the routed experts' operands; appended dense-expert tile: its own
   const T *act = static_cast<const T *>(ti.sh ? a.sh_act : a.act);
   const int32_t *perm = ti.sh ? nullptr : a.perm;
@@ -213,11 +214,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const TileInfo &ti,
     const int fg = blk >> 1, cb = blk & 1;
     const int c = kChunkElems<T> * unit_chunk(lane);
     if (GATEUP) {
-      const size_t f = static_cast<size_t>(ti.e) * a.m + nt0 * BN + fg * 16 + 8 * j + ur;
+      const size_t f = static_cast<size_t>(ti.e) * m + nt0 * BN + fg * 16 + 8 * j + ur;
       bsrc[t] = static_cast<const T *>(cb ? w1 : w0) + f * a.d + c;
     } else {
       const size_t n = static_cast<size_t>(ti.e) * a.d + nt0 * BN + fg * 32 + cb * 16 + 8 * j + ur;
-      bsrc[t] = static_cast<const T *>(w0) + n * a.m + c;
+      bsrc[t] = static_cast<const T *>(w0) + n * K + c;
     }
   }
   // fragment read offsets inside a 16-row block (two units) for k halves 0 and 1
@@ -233,7 +234,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const TileInfo &ti,
 #pragma unroll
     for (int c = 0; c < 2 * CW; ++c) acc[i][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   auto store_tile = [&](f32x4_t (&ac)[MW][2 * CW], int nt) {
-    store_tile_impl<T, GATEUP, MW, CW, RW, BN>(a, ti, outp, ac, nt, wr, wc, r16, g);
+    store_tile_impl<T, GATEUP, MW, CW, RW, BN>(GATEUP ? m : a.d, ti, outp, ac, nt, wr, wc, r16, g);
   };
 
   const int nk = K / BK;
@@ -364,33 +365,48 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const TileInfo &ti,
 // tile width in features (gate/up) or output columns (down) for CG column groups
 template <bool GATEUP> constexpr int tile_width(int cg) { return GATEUP ? 16 * cg : 32 * cg; }
 
+// OWN: a dense expert of another width is there (a kernel of its own: the selects of the
+// width in the common one cost the matrix-bound tiles 3%).
 // TPW (1 or 2): N tiles per workgroup, consecutive tiles of one M tile in one
 // pipeline (gemm_tile).
-template <typename T, bool GATEUP, int CG, int W, int TPW>
+template <typename T, bool GATEUP, int CG, int W, int TPW, bool OWN>
 __global__ __launch_bounds__(W * 64) void grouped_gemm_kernel(GemmArgs a) {
   static_assert(TPW == 1 || TPW == 2, "one or two N tiles per workgroup");
   const int nN = (GATEUP ? a.m : a.d) / tile_width<GATEUP>(CG);
-  const int nP = (nN + TPW - 1) / TPW;
-  int grp, np;
-  map_block(blockIdx.x, nP, &grp, &np);
-  const int nt0 = np * TPW, ntiles = min(TPW, nN - nt0);
-  const TileInfo ti = tile_info<sizeof(T) == 4 ? kTileMF32 : kTileM>(a, grp);
+  int grp, np, nt0, ntiles = 1;
+  constexpr int TM = sizeof(T) == 4 ? kTileMF32 : kTileM;
+  TileInfo ti;
+  if (GATEUP && OWN && static_cast<int>(blockIdx.x) >= a.sh_block0) {
+    // the dense expert's tiles, of a width other than the routed experts'
+    map_block(blockIdx.x - a.sh_block0, a.sh_m / tile_width<GATEUP>(CG), &grp, &nt0);
+    ti.e = 0;
+    ti.row0 = grp * TM;
+    ti.rows = min(TM, a.sh_rows - ti.row0);
+    ti.valid = ti.rows > 0;
+    ti.sh = true;
+    ti.once = a.sh_rows <= TM;
+  } else {
+    map_block(blockIdx.x, (nN + TPW - 1) / TPW, &grp, &np);
+    nt0 = np * TPW;
+    ntiles = min(TPW, nN - nt0);
+    ti = tile_info<TM>(a, grp);
+  }
   if (!ti.valid) return;
   __shared__ __align__(16) uint8_t smem[Pipe<16, CG, stage_halves<CG>(), W>::LDS];
   [[maybe_unused]] const int blocks = (ti.rows + 15) >> 4;
   // K rotation key: the expert (the appended dense expert gets its own)
   const int erot = ti.sh ? 0x155 : ti.e;
   if constexpr (sizeof(T) == 4) {  // tiles of at most 64 rows
-    gemm_tile<T, GATEUP, kTileMF32 / 16, CG, stage_halves<CG>(), W>(a, ti, nt0, ntiles, erot, smem);
+    gemm_tile<T, GATEUP, kTileMF32 / 16, CG, stage_halves<CG>(), W, OWN>(a, ti, nt0, ntiles, erot, smem);
   } else {
     if (blocks <= 4)
-      gemm_tile<T, GATEUP, 4, CG, stage_halves<CG>(), W>(a, ti, nt0, ntiles, erot, smem);
+      gemm_tile<T, GATEUP, 4, CG, stage_halves<CG>(), W, OWN>(a, ti, nt0, ntiles, erot, smem);
     else if (blocks <= 8)
-      gemm_tile<T, GATEUP, 8, CG, stage_halves<CG>(), W>(a, ti, nt0, ntiles, erot, smem);
+      gemm_tile<T, GATEUP, 8, CG, stage_halves<CG>(), W, OWN>(a, ti, nt0, ntiles, erot, smem);
     else if (blocks <= 12)
-      gemm_tile<T, GATEUP, 12, CG, stage_halves<CG>(), W>(a, ti, nt0, ntiles, erot, smem);
+      gemm_tile<T, GATEUP, 12, CG, stage_halves<CG>(), W, OWN>(a, ti, nt0, ntiles, erot, smem);
     else
-      gemm_tile<T, GATEUP, 16, CG, stage_halves<CG>(), W>(a, ti, nt0, ntiles, erot, smem);
+      gemm_tile<T, GATEUP, 16, CG, stage_halves<CG>(), W, OWN>(a, ti, nt0, ntiles, erot, smem);
   }
 }
 
@@ -413,11 +429,29 @@ unsigned grid_for(int max_groups, int nN) {
 
 template <typename T, bool GATEUP, int CG, int TPW> void launch_grouped(const GemmArgs &a, hipStream_t stream) {
   const int nN = (GATEUP ? a.m : a.d) / tile_width<GATEUP>(CG);
-  grouped_gemm_kernel<T, GATEUP, CG, kGemmWaves, TPW>
-      <<<dim3(grid_for(a.max_groups, pairs(nN, TPW))), kGemmWaves * 64, 0, stream>>>(a);
+  const unsigned grid = grid_for(a.max_groups, pairs(nN, TPW));
+  if (a.sh_tiles == 0 || a.sh_m == a.m) {
+    grouped_gemm_kernel<T, GATEUP, CG, kGemmWaves, TPW, false><<<dim3(grid), kGemmWaves * 64, 0, stream>>>(a);
+    return;
+  }
+  GemmArgs b = a;
+  unsigned own = 0;
+  if (GATEUP) {
+    b.sh_tiles = 0;
+    b.sh_block0 = static_cast<int>(grid);
+    own = grid_for(a.sh_tiles, a.sh_m / tile_width<GATEUP>(CG));
+  }
+  grouped_gemm_kernel<T, GATEUP, CG, kGemmWaves, TPW, true><<<dim3(grid + own), kGemmWaves * 64, 0, stream>>>(b);
 }
 
+// column groups of the gate/up tiles for an intermediate size
+int gateup_cg(int m, bool bf16) { return !bf16 ? 2 : m % tile_width<true>(8) == 0 ? 8 : 4; }
+
 }  // namespace
+
+bool gateup_takes_dense(int m, int sh_m, bool bf16) {
+  return sh_m % tile_width<true>(gateup_cg(m, bf16)) == 0;
+}
 
 // bf16: 128 features per gate/up tile when they divide m, else 64; 256 output columns
 // per down tile when they divide d, else 128.  fp32: 32 features, 64 columns.
@@ -425,7 +459,7 @@ hipError_t launch_gateup(const GemmArgs &a, bool bf16, hipStream_t stream) {
   if (a.max_groups <= 0) return hipSuccess;
   if (!bf16)
     launch_grouped<float, true, 2, 1>(a, stream);
-  else if (a.m % tile_width<true>(8) == 0)
+  else if (gateup_cg(a.m, true) == 8)
     launch_grouped<bf16_t, true, 8, kTpwGateUp>(a, stream);
   else
     launch_grouped<bf16_t, true, 4, kTpwGateUp>(a, stream);

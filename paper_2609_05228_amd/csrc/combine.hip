@@ -61,7 +61,9 @@ template <> struct V<float> {
   static __device__ __forceinline__ void load4(const float *p, float v[4]) { cvt(load(p), v); }
 };
 
-template <typename T>
+// SHP: the shared expert comes as partial sums (small batches; the registers of their loads
+// in the common kernel cost 4096 tokens 3 us)
+template <typename T, bool SHP>
 __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
   constexpr int VN = V<T>::n;
   __shared__ int rows[kMaxK];
@@ -83,8 +85,8 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
       if (rows[i] >= 0) q[i] = V<T>::load(Y + static_cast<size_t>(rows[i]) * a.d + c);
     typename V<T>::raw qs;
     if (Ys) qs = V<T>::load(Ys + static_cast<size_t>(t) * a.d + c);
-    float sh[VN];
-    if (a.Yspart) {
+    [[maybe_unused]] float sh[VN];
+    if constexpr (SHP) {
       // the shared expert's partial sums, every load in flight before the first add
       float4 p[kMaxSplits][VN / 4];
 #pragma unroll
@@ -124,7 +126,7 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
 #pragma unroll
       for (int j = 0; j < VN; ++j) acc[j] += v[j];
     }
-    if (a.Yspart) {
+    if constexpr (SHP) {
 #pragma unroll
       for (int j = 0; j < VN; ++j) acc[j] += sh[j];
     }
@@ -214,10 +216,15 @@ hipError_t launch_combine(const CombineArgs &a, bool bf16, hipStream_t stream) {
       combine_split_kernel<bf16_t><<<grid, 256, 0, stream>>>(a);
     else
       combine_split_kernel<float><<<grid, 256, 0, stream>>>(a);
+  } else if (a.Yspart) {
+    if (bf16)
+      combine_kernel<bf16_t, true><<<dim3(a.T), 256, 0, stream>>>(a);
+    else
+      combine_kernel<float, true><<<dim3(a.T), 256, 0, stream>>>(a);
   } else if (bf16) {
-    combine_kernel<bf16_t><<<dim3(a.T), 256, 0, stream>>>(a);
+    combine_kernel<bf16_t, false><<<dim3(a.T), 256, 0, stream>>>(a);
   } else {
-    combine_kernel<float><<<dim3(a.T), 256, 0, stream>>>(a);
+    combine_kernel<float, false><<<dim3(a.T), 256, 0, stream>>>(a);
   }
   return hipGetLastError();
 }

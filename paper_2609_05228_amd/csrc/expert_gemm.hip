@@ -21,10 +21,10 @@
 //    through two LDS rings in 160 KB: activations (L2-resident) 2-4 K stages deep,
 //    expert weights (from HBM; with the non-temporal hint when no other M tile
 //    reads them) 3-8 stages deep; each wave waits only for the
-//    stage it computes next (vmcnt counted exactly from the issue schedule; with
-//    two activation stages one of two constants, since a run-time count becomes a
-//    branch tree that costs matrix-bound tiles several percent), then one barrier
-//    per K step;
+//    stage it computes next (vmcnt counted exactly from the issue schedule, in closed
+//    form: one of two constants with two activation stages, else of a few, since a
+//    64-way choice is a branch tree that costs matrix-bound tiles several percent),
+//    then one barrier per K step;
 //  * one DMA instruction moves 8 rows x 128 bytes (whole cache lines) and lane i
 //    lands at byte 16*i; the chunk a lane fetches is XOR-swizzled by its row so
 //    the MFMA fragment reads (16 rows x 16 bytes) are bank-conflict free;
@@ -109,8 +109,8 @@ constexpr int kGemmWaves = 8;  // waves per workgroup (two per SIMD)
 // one with deeper rings: the stream rate, not the bytes in flight, is the limit.
 template <int CG> constexpr int stage_halves() { return 2; }
 
-// Pipe, cum_ops and pending_ok (gemm_pipe.h): ring depths per tile shape and
-// the exact wait counts of a wave's DMA issue sequence.
+// Pipe, Closed and Pending (gemm_pipe.h): ring depths per tile shape and the exact
+// wait counts of a wave's DMA issue sequence.
 
 // Output stores of gemm_tile: lane holds column r16 of each block, rows 4*g + q.
 template <typename T, bool GATEUP, int MW, int CW, int RW, int BN>

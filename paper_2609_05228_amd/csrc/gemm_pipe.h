@@ -50,7 +50,8 @@ __host__ __device__ inline int cum_ops(int j, int nk, int na) {
          pipe_max(0, pipe_min(j, nk - P::SB + 1)) * P::NB;
 }
 
-// DMAs that may still be outstanding at the wait before stage kt's compute:
+// The count that the closed forms below (Closed, Pending) are checked against on the
+// host: DMAs that may still be outstanding at the wait before stage kt's compute:
 // everything issued after the later of A(kt) and B(kt) (vmcnt completes in
 // issue order).  na = this wave's A DMAs per stage.
 template <class P>

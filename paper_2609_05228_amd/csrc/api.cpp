@@ -83,7 +83,11 @@ Layout layout_of(const ace_moe_desc &d, bool split_down, bool split_shared) {
   L.sspart = take(static_cast<size_t>(L.ksplit) * T * 4);
   L.local_rank = take(slots);
   L.chunk_count = take(static_cast<size_t>(L.G) * N);
-  L.chunk_base = take(static_cast<size_t>(L.G) * N * 4);
+  // fp32's tile lists are longer (64-row tiles), so there the plan's chunk bases lie in H,
+  // which the gate/up launch writes after the plan has read them: no layer needs more
+  // scratch than with 256-row tiles
+  const bool bases_in_h = L.tile_m == ace::kTileMF32;
+  if (!bases_in_h) L.chunk_base = take(static_cast<size_t>(L.G) * N * 4);
   L.slot_row = take(slots * 4);
   L.gates = take(slots * 4);
   L.counts = take(N * 4);
@@ -95,6 +99,7 @@ Layout layout_of(const ace_moe_desc &d, bool split_down, bool split_shared) {
   L.tile_ord = take(static_cast<size_t>(L.max_groups) * 4);
   L.n_tiles = take(4);
   L.H = take(slots * m * esz);
+  if (bases_in_h) L.chunk_base = L.H;  // G N 4 <= (T + 15) 64 bytes of at least 256 T k
   L.Y = take(slots * dd * esz);
   if (d.n_shared > 0) {
     L.Hs = take(T * static_cast<size_t>(d.m_shared) * esz);

@@ -369,16 +369,19 @@ template <bool GATEUP> constexpr int tile_width(int cg) { return GATEUP ? 16 * c
 // width in the common one cost the matrix-bound tiles 3%).
 // TPW (1 or 2): N tiles per workgroup, consecutive tiles of one M tile in one
 // pipeline (gemm_tile).
-template <typename T, bool GATEUP, int CG, int W, int TPW, bool OWN>
+// ROWS: the grid has several rows (launch_grouped; the row index in the common kernel cost
+// fp32 layers of 65-200 tokens 0.2-0.8 us).
+template <typename T, bool GATEUP, int CG, int W, int TPW, bool OWN, bool ROWS = false>
 __global__ __launch_bounds__(W * 64) void grouped_gemm_kernel(GemmArgs a) {
   static_assert(TPW == 1 || TPW == 2, "one or two N tiles per workgroup");
   const int nN = (GATEUP ? a.m : a.d) / tile_width<GATEUP>(CG);
+  const int block = static_cast<int>(ROWS ? (blockIdx.y << kPipeGridRow) + blockIdx.x : blockIdx.x);
   int grp, np, nt0, ntiles = 1;
   constexpr int TM = sizeof(T) == 4 ? kTileMF32 : kTileM;
   TileInfo ti;
-  if (GATEUP && OWN && static_cast<int>(blockIdx.x) >= a.sh_block0) {
+  if (GATEUP && OWN && block >= a.sh_block0) {
     // the dense expert's tiles, of a width other than the routed experts'
-    map_block(blockIdx.x - a.sh_block0, a.sh_m / tile_width<GATEUP>(CG), &grp, &nt0);
+    map_block(block - a.sh_block0, a.sh_m / tile_width<GATEUP>(CG), &grp, &nt0);
     ti.e = 0;
     ti.row0 = grp * TM;
     ti.rows = min(TM, a.sh_rows - ti.row0);
@@ -386,7 +389,7 @@ __global__ __launch_bounds__(W * 64) void grouped_gemm_kernel(GemmArgs a) {
     ti.sh = true;
     ti.once = a.sh_rows <= TM;
   } else {
-    map_block(blockIdx.x, (nN + TPW - 1) / TPW, &grp, &np);
+    map_block(block, (nN + TPW - 1) / TPW, &grp, &np);
     nt0 = np * TPW;
     ntiles = min(TPW, nN - nt0);
     ti = tile_info<TM>(a, grp);
@@ -427,21 +430,35 @@ unsigned grid_for(int max_groups, int nN) {
   return static_cast<unsigned>(8 * nN * g8);
 }
 
+// A launch takes fewer than 2^32 threads in x.  bf16 tiles are so large that the grid stays
+// far below; fp32's 64-row tiles reach it at slots * m = 2^34 (an H of 64 GiB: 2^20 tokens,
+// top-8, experts of 2048), where the grid gets several rows.
 template <typename T, bool GATEUP, int CG, int TPW> void launch_grouped(const GemmArgs &a, hipStream_t stream) {
   const int nN = (GATEUP ? a.m : a.d) / tile_width<GATEUP>(CG);
   const unsigned grid = grid_for(a.max_groups, pairs(nN, TPW));
-  if (a.sh_tiles == 0 || a.sh_m == a.m) {
-    grouped_gemm_kernel<T, GATEUP, CG, kGemmWaves, TPW, false><<<dim3(grid), kGemmWaves * 64, 0, stream>>>(a);
-    return;
-  }
   GemmArgs b = a;
-  unsigned own = 0;
-  if (GATEUP) {
+  unsigned blocks = grid;
+  const bool own = a.sh_tiles > 0 && a.sh_m != a.m;
+  if (own && GATEUP) {
     b.sh_tiles = 0;
     b.sh_block0 = static_cast<int>(grid);
-    own = grid_for(a.sh_tiles, a.sh_m / tile_width<GATEUP>(CG));
+    blocks += grid_for(a.sh_tiles, a.sh_m / tile_width<GATEUP>(CG));
   }
-  grouped_gemm_kernel<T, GATEUP, CG, kGemmWaves, TPW, true><<<dim3(grid + own), kGemmWaves * 64, 0, stream>>>(b);
+  const PipeGrid p = sizeof(T) == 4 ? pipe_grid(blocks, kGemmWaves * 64) : PipeGrid{blocks, 1};
+  const dim3 dims(p.x, p.y);
+  auto launch = [&](auto kernel) { kernel<<<dims, kGemmWaves * 64, 0, stream>>>(b); };
+  if constexpr (sizeof(T) == 4)
+    if (p.y > 1) {
+      if (own)
+        launch(grouped_gemm_kernel<T, GATEUP, CG, kGemmWaves, TPW, true, true>);
+      else
+        launch(grouped_gemm_kernel<T, GATEUP, CG, kGemmWaves, TPW, false, true>);
+      return;
+    }
+  if (own)
+    launch(grouped_gemm_kernel<T, GATEUP, CG, kGemmWaves, TPW, true>);
+  else
+    launch(grouped_gemm_kernel<T, GATEUP, CG, kGemmWaves, TPW, false>);
 }
 
 // column groups of the gate/up tiles for an intermediate size

@@ -100,4 +100,16 @@ template <class P> struct Closed {
   __host__ __device__ static bool nb_pending(int kt, int nk) { return kt >= 1 && kt + P::SB - 2 < nk; }
 };
 
+// Grid of `blocks` workgroups of `threads`: a launch takes fewer than 2^32 threads in x, so
+// larger grids are rows of 2^kPipeGridRow blocks, block (y << kPipeGridRow) + x (a multiple of
+// 8 in a row, so block b runs on XCD b % 8 either way); the last row's excess is past the end.
+constexpr int kPipeGridRow = 22;
+struct PipeGrid {
+  unsigned x, y;
+};
+inline PipeGrid pipe_grid(unsigned long long blocks, unsigned threads) {
+  if (blocks * threads < 1ull << 32) return {static_cast<unsigned>(blocks), 1};
+  return {1u << kPipeGridRow, static_cast<unsigned>((blocks + (1ull << kPipeGridRow) - 1) >> kPipeGridRow)};
+}
+
 }  // namespace ace

@@ -106,10 +106,9 @@ template <typename T>
 __global__ __launch_bounds__(256, 2) void gsp_tile_kernel(TabArgs a) {
   constexpr int KL = Vec<T>::n;  // consecutive k of a lane
   // experts dealt to the 8 XCDs, so the tile pairs of one expert share its weights in one L2
-  const int b = blockIdx.x >> 3;
-  const int e = (blockIdx.x & 7) + 8 * (b / a.n_pairs);
+  const int e = (blockIdx.x & 7) + 8 * blockIdx.y;
   if (e >= a.N) return;
-  int p = b % a.n_pairs, bi = 0;
+  int p = blockIdx.x >> 3, bi = 0;
   const int pair = p;
   while (p >= a.mt - bi) {
     p -= a.mt - bi;
@@ -277,8 +276,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void rcr_hidden_kernel(TabArgs a) {
   constexpr int KL = Vec<T>::n;
   __shared__ double red[4];
-  const int nb = a.m / (4 * kHRows);
-  const int e = blockIdx.x / nb, blk = blockIdx.x - e * nb;
+  const int e = blockIdx.y, blk = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int d = a.d, m = a.m;
   const T *wr = static_cast<const T *>(a.w_router) + static_cast<size_t>(e) * d;
@@ -350,7 +348,7 @@ __global__ __launch_bounds__(256) void rcr_out_kernel(TabArgs a) {
   constexpr int KL = Vec<T>::n;
   __shared__ double red[4];
   const int nb = a.d / (4 * kFRows);
-  const int e = blockIdx.x / nb, blk = blockIdx.x - e * nb;
+  const int e = blockIdx.y, blk = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int d = a.d, m = a.m;
   const T *Wd = static_cast<const T *>(a.w_down) +
@@ -432,12 +430,14 @@ __global__ __launch_bounds__(256) void tables_finalize_kernel(TabArgs a) {
   }
 }
 
+// Experts lie in the grids' y: a launch takes fewer than 2^32 threads in x (512 experts of
+// 16384 have 2^24 tile pairs).
 template <typename T>
 void launch_tables_t(const TabArgs &a, hipStream_t stream) {
-  gsp_tile_kernel<T><<<dim3(8 * ((a.N + 7) / 8) * a.n_pairs), 256, 0, stream>>>(a);
+  gsp_tile_kernel<T><<<dim3(8 * a.n_pairs, (a.N + 7) / 8), 256, 0, stream>>>(a);
   rcr_mean_kernel<T><<<dim3((a.d + 63) / 64), 256, 0, stream>>>(a);
-  rcr_hidden_kernel<T><<<dim3(a.N * (a.m / (4 * kHRows))), 256, 0, stream>>>(a);
-  rcr_out_kernel<T><<<dim3(a.N * (a.d / (4 * kFRows))), 256, 0, stream>>>(a);
+  rcr_hidden_kernel<T><<<dim3(a.m / (4 * kHRows), a.N), 256, 0, stream>>>(a);
+  rcr_out_kernel<T><<<dim3(a.d / (4 * kFRows), a.N), 256, 0, stream>>>(a);
   tables_expert_kernel<<<dim3(a.N), 256, 0, stream>>>(a);
   tables_finalize_kernel<<<1, 256, 0, stream>>>(a);
 }

@@ -41,3 +41,30 @@ def test_fp32_gemm_past_one_grid_row():
         half = run(x[rows])
         for key in ("y", "topk_idx", "keep", "gates"):
             assert torch.equal(whole[key][rows], half[key]), key
+
+
+@pytest.mark.gpu
+def test_tables_past_one_grid_row():
+    """512 experts of 16384: 2^24 and some tile pairs in all, of 256 threads each.  Against
+    the definition in fp64 (summation order: 1e-12 relative, as for the small shapes)."""
+    if torch.cuda.mem_get_info()[0] < 24 << 30:
+        pytest.skip("needs 24 GiB of free device memory")
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    d, N, m, eps = 32, 512, 16384, 1e-6
+    w = {n: _normal(gen, s, *shape).bfloat16() for n, s, shape in (
+        ("gamma", 1.0, (d,)), ("w_router", 0.1, (N, d)), ("w_gate", 0.05, (N, m, d)), ("w_up", 0.05, (N, m, d)),
+        ("w_down", 0.05, (N, d, m)))}
+    got = ace.build_tables(w, want_f64=True)
+    torch.cuda.synchronize()
+    gam, wr = w["gamma"].double(), w["w_router"].double()
+    wr = wr - wr.mean(dim=0)
+    q = wr / (wr.square().mean(dim=1, keepdim=True).sqrt() + eps)
+    gsp, rcr = [], []
+    for e in range(N):
+        wg, wu, wd = (w[n][e].double() for n in ("w_gate", "w_up", "w_down"))
+        G, U = wg * gam, wu * gam
+        gsp.append((U.norm() * (wd @ G).norm() * G.norm() * (wd @ U).norm()).sqrt())
+        h = wg @ q[e]
+        rcr.append((wd @ (h * torch.sigmoid(h) * (wu @ q[e]))).norm() / (q[e].norm() + eps))
+    for key, raw in (("a_gsp64", torch.stack(gsp)), ("a_rcr64", torch.stack(rcr))):
+        torch.testing.assert_close(got[key], raw / (raw.mean() + eps), rtol=1e-12, atol=0.0)

@@ -354,12 +354,16 @@ __host__ __device__ inline int shared_items(const SkinnyArgs &sa, bool gateup) {
 
 // WGS = 0: one wave per work item, item = ((grp * splits) + s) * nN + nb, four
 // independent waves per workgroup.  WGS = splits (gate/up): workgroup
-// grp * nN + nb, wave s; the waves add their partial sums through LDS.  The dense
-// expert's items come first (it has every token's row): as two unsplit launches of
-// their own they took 8-29 us of a small batch (3 tokens, 1792 hidden, 38 experts of
-// 128 and a shared one: 35.7 us a layer, now 23.7; 33 tokens, 2048 hidden, a shared
-// expert of 1024: 81.2, now 52.0).
-template <typename T, bool GATEUP, int WGS>
+// grp * nN + nb, wave s; the waves add their partial sums through LDS.
+// A dense expert's items come first (it has every token's row): as two unsplit launches of
+// their own they took 8-29 us of a small batch (3 tokens, 1792 hidden, 38 experts of 128
+// and a shared one: 35.7 us a layer, now 23.7; 33 tokens, 2048 hidden, a shared expert of
+// 1024: 81.2, now 52.0).
+// PLAIN (gate/up): no dense expert and no self_plan, neither choice compiled.  With them in
+// the one kernel a token's gate/up took 8.16 us (8.04 before the dense expert came in),
+// now 7.64; layers of 2-16 tokens 0.2-1.7% faster.  Down keeps the common kernel: compiled
+// without the dense expert it was no faster up to 16 tokens and 0.2-0.5 us slower above.
+template <typename T, bool GATEUP, int WGS, bool PLAIN>
 __global__ __launch_bounds__((WGS ? WGS : kSkinnyWavesPerGroup) * 64) void skinny_gemm_kernel(SkinnyArgs sa) {
   constexpr int NW = WGS ? WGS : kSkinnyWavesPerGroup;
   static_assert(!WGS || GATEUP, "workgroup reduction: gate/up only");
@@ -370,10 +374,10 @@ __global__ __launch_bounds__((WGS ? WGS : kSkinnyWavesPerGroup) * 64) void skinn
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint8_t *ring = smem + wave * kSkinnyRingBytes;
   f32x4_t *red = WGS ? reinterpret_cast<f32x4_t *>(smem) : nullptr;
-  const int nS = shared_items(sa, GATEUP);
+  const int nS = PLAIN ? 0 : shared_items(sa, GATEUP);
   const long first = static_cast<long>(nS) * (WGS ? NW : 1);  // first routed item
   const long item = static_cast<long>(blockIdx.x) * NW + wave - first;
-  const bool shared = item < 0;
+  const bool shared = !PLAIN && item < 0;
   int nb, s, grp = 0;
   if constexpr (WGS > 0) {
     const int b = static_cast<int>(blockIdx.x) - nS;
@@ -398,8 +402,9 @@ __global__ __launch_bounds__((WGS ? WGS : kSkinnyWavesPerGroup) * 64) void skinn
     op = Op{a.sh_act, a.sh_w0, a.sh_w1, a.sh_out, nullptr, sa.sh_part, a.sh_m, GATEUP ? sa.splits : sa.sh_splits,
             a.sh_rows, false};
   } else {
-    ti = (GATEUP && sa.self_plan) ? self_tile(sa, grp, nb == 0 && s == 0, item == 0, &tok) : skinny_tile(a, grp);
-    op = Op{a.act, a.w0, a.w1, a.out, a.perm, sa.part, a.m, sa.splits, sa.rows_cap, sa.self_plan};
+    const bool self_plan = !PLAIN && sa.self_plan;
+    ti = (GATEUP && self_plan) ? self_tile(sa, grp, nb == 0 && s == 0, item == 0, &tok) : skinny_tile(a, grp);
+    op = Op{a.act, a.w0, a.w1, a.out, a.perm, sa.part, a.m, sa.splits, sa.rows_cap, self_plan};
   }
   if (!ti.valid) return;
   const int blocks = (ti.rows + 15) >> 4;
@@ -425,23 +430,24 @@ __global__ __launch_bounds__((WGS ? WGS : kSkinnyWavesPerGroup) * 64) void skinn
   }
 }
 
-template <typename T> hipError_t launch_skinny_t(const SkinnyArgs &sa, bool gateup, hipStream_t stream) {
+template <typename T, bool PLAIN> hipError_t launch_skinny_t(const SkinnyArgs &sa, bool gateup, hipStream_t stream) {
   const GemmArgs &a = sa.g;
   const long nN = gateup ? a.m / 16 : a.d / 32;
-  const long items = static_cast<long>(a.max_groups) * sa.splits * nN + shared_items(sa, gateup);
+  const long nS = shared_items(sa, gateup);
+  const long items = static_cast<long>(a.max_groups) * sa.splits * nN + nS;
   const dim3 grid(static_cast<unsigned>((items + kSkinnyWavesPerGroup - 1) / kSkinnyWavesPerGroup));
   if (gateup) {
     // several K splits: the splits of a 16-feature block are one workgroup's waves
-    const dim3 wg_grid(static_cast<unsigned>(static_cast<long>(a.max_groups) * nN + shared_items(sa, gateup)));
+    const dim3 wg_grid(static_cast<unsigned>(static_cast<long>(a.max_groups) * nN + nS));
     switch (sa.splits) {
-      case 1: skinny_gemm_kernel<T, true, 0><<<grid, kSkinnyWavesPerGroup * 64, 0, stream>>>(sa); break;
-      case 2: skinny_gemm_kernel<T, true, 2><<<wg_grid, 2 * 64, 0, stream>>>(sa); break;
-      case 4: skinny_gemm_kernel<T, true, 4><<<wg_grid, 4 * 64, 0, stream>>>(sa); break;
-      case 8: skinny_gemm_kernel<T, true, 8><<<wg_grid, 8 * 64, 0, stream>>>(sa); break;
+      case 1: skinny_gemm_kernel<T, true, 0, PLAIN><<<grid, kSkinnyWavesPerGroup * 64, 0, stream>>>(sa); break;
+      case 2: skinny_gemm_kernel<T, true, 2, PLAIN><<<wg_grid, 2 * 64, 0, stream>>>(sa); break;
+      case 4: skinny_gemm_kernel<T, true, 4, PLAIN><<<wg_grid, 4 * 64, 0, stream>>>(sa); break;
+      case 8: skinny_gemm_kernel<T, true, 8, PLAIN><<<wg_grid, 8 * 64, 0, stream>>>(sa); break;
       default: return hipErrorInvalidValue;
     }
   } else {
-    skinny_gemm_kernel<T, false, 0><<<grid, kSkinnyWavesPerGroup * 64, 0, stream>>>(sa);
+    skinny_gemm_kernel<T, false, 0, PLAIN><<<grid, kSkinnyWavesPerGroup * 64, 0, stream>>>(sa);
   }
   return hipGetLastError();
 }
@@ -450,7 +456,9 @@ template <typename T> hipError_t launch_skinny_t(const SkinnyArgs &sa, bool gate
 
 hipError_t launch_skinny(const SkinnyArgs &sa, bool gateup, bool bf16, hipStream_t stream) {
   if (sa.g.max_groups <= 0) return hipSuccess;
-  return bf16 ? launch_skinny_t<bf16_t>(sa, gateup, stream) : launch_skinny_t<float>(sa, gateup, stream);
+  if (gateup && sa.g.sh_tiles == 0 && !sa.self_plan)
+    return bf16 ? launch_skinny_t<bf16_t, true>(sa, gateup, stream) : launch_skinny_t<float, true>(sa, gateup, stream);
+  return bf16 ? launch_skinny_t<bf16_t, false>(sa, gateup, stream) : launch_skinny_t<float, false>(sa, gateup, stream);
 }
 
 }  // namespace ace

@@ -447,7 +447,7 @@ template <typename T, bool PLAIN> hipError_t launch_skinny_t(const SkinnyArgs &s
       default: return hipErrorInvalidValue;
     }
   } else {
-    skinny_gemm_kernel<T, false, 0, PLAIN><<<grid, kSkinnyWavesPerGroup * 64, 0, stream>>>(sa);
+    skinny_gemm_kernel<T, false, 0, false><<<grid, kSkinnyWavesPerGroup * 64, 0, stream>>>(sa);
   }
   return hipGetLastError();
 }

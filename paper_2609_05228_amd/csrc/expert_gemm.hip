@@ -35,11 +35,11 @@
 //  * the down launch gives each workgroup two N tiles of one M tile, run as one
 //    pipeline (the second tile's first stages load under the first's last steps).
 // fp32 path: the same tile body on 32-wide K stages, four v_mfma_f32_16x16x4f32 per
-// pair of fragments.  An fp32 multiply takes 16 times the matrix time per byte, so
-// the matrix cores bound all but the shortest tiles, and what counts is to spread
-// the work evenly: M tiles of 64 rows (the plan's tile size for fp32 layers), 32
-// features or 64 columns wide, half the LDS each, so two workgroups share a CU and
-// one's ramp and stores run under the other's K loop.  The kernels that loaded one
+// pair of fragments.  By the peak rates an fp32 multiply takes 16 times the matrix time
+// of a bf16 one, 8 times per byte of operand, so the matrix cores bound all but the
+// shortest tiles, and what counts is to spread the work evenly: M tiles of 64 rows (the
+// plan's tile size for fp32 layers), 32 features or 64 columns wide, half the LDS each, so
+// two workgroups share a CU and one's ramp and stores run under the other's K loop.  The kernels that loaded one
 // 16-wide K step at a time between barriers took 199 + 105 us for 517 tokens (1024
 // hidden, 32 experts of 512, top-4), 256-row tiles with all of the LDS 63 + 35, half
 // of it 53 + 29; 929 tokens on 11 experts take 159 us a layer with 256-row tiles,

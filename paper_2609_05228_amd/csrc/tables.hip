@@ -97,8 +97,12 @@ __device__ __forceinline__ double wave_sum(double v) {
 // multiplied; read straight from L2 at every K block the kernel took 9.2 ms, and with
 // the next block's loads in registers they spill (15 ms).  Two waves per SIMD; three
 // measured the same.
-// gamma enters one operand of each product as gamma^2 (exact in fp64: 8 or 24 + 16
-// or 48 bits against one weight), which halves the fp64 multiplies.  Row r of a
+// gamma enters one operand of each product as gamma^2, which halves the fp64
+// multiplies.  gamma^2 is exact in fp64 (16 bits of bf16, 48 of fp32), and so is its
+// product with a bf16 weight (24 bits); with an fp32 weight (72 bits) that is rounded
+// once.  The fp32 tables do not show it: their experts spread 1.0-1.5e-16 (rms, relative)
+// around sums with a 64-bit mantissa, as with gamma on both operands (six shapes of
+// 128-2048 hidden, 64-256 experts of 64-192).  Row r of a
 // sub-tile's 16-row block u is row 2 r + u, so W_down is read in adjacent column
 // pairs.  In a diagonal tile the sub-tile below the diagonal mirrors the one above
 // it: its wave does nothing and the other counts twice.

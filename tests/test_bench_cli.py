@@ -37,3 +37,20 @@ def test_source_digest_ignores_comments(tmp_path, monkeypatch):
     (csrc / "k.hip").write_text("int f(int x) { return x + 1; }\n")
     (csrc / "h.h").write_text("#pragma once\nconstexpr int kA = 5;\n")
     assert bench.source_digest("k.hip") != d0
+
+
+def test_traffic_record_names_the_stages_kernels():
+    """Each stage's kernel is in the committed record, and is defined in its source with as
+    many template parameters (a renamed kernel made the traffic null)."""
+    import json
+    import re
+
+    import bench
+
+    recorded = json.load(open(bench.TRAFFIC))["bytes_per_dispatch"]
+    for name, src in bench.STAGE_KERNEL.values():
+        assert name in recorded, name
+        kernel, args = name.rstrip(">").split("<")
+        text = open(os.path.join(ROOT, "paper_2609_05228_amd", "csrc", src), encoding="utf-8").read()
+        found = re.search(r"template <([^>]*)>\s*__global__[^;{]*?\b" + kernel + r"\(", text)
+        assert found and len(found.group(1).split(",")) == len(args.split(",")), name
